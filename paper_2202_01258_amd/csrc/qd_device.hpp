@@ -158,10 +158,10 @@ __device__ __forceinline__ float div_rcp(float a, float b) {
 }
 
 // tanh: odd Taylor polynomial through x^11 for |x| < 0.3,
-// else 1 - 2 / (e^{2|x|} + 1); the sign is copied back.  FAST takes the
-// quotient from div_rcp (same bits for every fp32 input).
+// else 1 - 2 / (e^{2|x|} + 1) with e^y by exp32's formula; the sign is copied
+// back.  FAST takes the quotient from div_rcp (same bits for every fp32 input).
 template <bool FAST = true>
-__device__ __forceinline__ float tanh32(float x) {
+__device__ __forceinline__ float tanh32_plain(float x) {
   const float a = __builtin_fabsf(x);
   float r;
   if (a < 0.3f) {
@@ -176,6 +176,48 @@ __device__ __forceinline__ float tanh32(float x) {
     r = 1.0f - (FAST ? div_rcp(2.0f, d) : 2.0f / d);
   }
   return __builtin_copysignf(r, x);
+}
+
+// tanh32_plain<true> bit for bit (qd_check_fast_arith compares all 2^32
+// inputs), without its branch and with fewer instructions.  Nearly every wave
+// holds both kinds of lanes, so both sides are evaluated and one is selected:
+// two chains side by side instead of one after the other.
+//   * small side on x itself, every step being odd or even in x (the sign of
+//     a zero is put back with the others');
+//   * e^{2a}: with h = min(a, 44), the doubling goes into the constants (a
+//     power of two commutes with every rounding here): k = rint(h 2 log2 e),
+//     r/2 = h - k ln 2 / 2, and the Horner coefficient of r^i times 2^i.  The
+//     integer k is the low mantissa bits of h 2 log2 e + 1.5 2^23, rounded
+//     once (at 62 inputs k is exp32's neighbour, with the same tanh), so 2^k
+//     goes into p's exponent by one shift-and-add (k <= 127, p in [0.7, 1.42));
+//   * 2 / d as the corrected reciprocal of d / 2;
+//   * a NaN takes the small side, which returns it.
+__device__ __forceinline__ float tanh32(float x) {
+  const float x2 = x * x;
+  float q = fma32(x2, -1382.0f / 155925.0f, 62.0f / 2835.0f);
+  q = fma32(x2, q, -17.0f / 315.0f);
+  q = fma32(x2, q, 2.0f / 15.0f);
+  q = fma32(x2, q, -1.0f / 3.0f);
+  const float low = fma32(x * x2, q, x);
+  const float a = __builtin_fabsf(x);
+  const float h = __builtin_fminf(a, 44.0f);
+  constexpr float kMagic = 0x1.8p+23f;
+  const float t = fma32(h, 2.0f * kLog2e, kMagic);
+  const float k = t - kMagic;
+  float r = fma32(k, -0.5f * kLn2Hi, h);
+  r = fma32(k, -0.5f * kLn2Lo, r);
+  float p = fma32(r, 128.0f * (1.0f / 5040.0f), 64.0f * (1.0f / 720.0f));
+  p = fma32(r, p, 32.0f * (1.0f / 120.0f));
+  p = fma32(r, p, 16.0f * (1.0f / 24.0f));
+  p = fma32(r, p, 8.0f * (1.0f / 6.0f));
+  p = fma32(r, p, 4.0f * 0.5f);
+  p = fma32(r, p, 2.0f);
+  p = fma32(r, p, 1.0f);
+  const float e = __uint_as_float(__float_as_uint(p) + (__float_as_uint(t) << 23));
+  const float half_d = fma32(e, 0.5f, 0.5f);
+  const float y = __builtin_amdgcn_rcpf(half_d);
+  const float high = 1.0f - fma32(fma32(-y, half_d, 1.0f), y, y);
+  return __builtin_copysignf(a >= 0.3f ? high : low, x);
 }
 
 // 1 / (1 + e^{-x}); FAST as for tanh32 (same bits for |x| <= 1, the range of
@@ -205,11 +247,24 @@ __device__ __forceinline__ float row_shl(float v) {
 }
 template <int N>
 __device__ __forceinline__ float row_ror(float v) {
-  return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0x120 + N, 0xf, 0xf, false));
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0x120 + N, 0xf, 0xf, true));
 }
 template <int N>
 __device__ __forceinline__ int row_ror(int v) {
-  return (int)__builtin_amdgcn_update_dpp(0u, (uint32_t)v, 0x120 + N, 0xf, 0xf, false);
+  return (int)__builtin_amdgcn_update_dpp(0u, (uint32_t)v, 0x120 + N, 0xf, 0xf, true);
+}
+
+// Lanes 0 .. 7 of each row of 16 lanes, in every lane of the row.  One block:
+// between separate broadcasts the compiler places waits that these do not need
+// (no VGPR that a DPP instruction reads may be written by either of the two
+// instructions before it, which the s_nop sees to).
+#define QD_ROW_BCAST(K) "v_mov_b32_dpp %" #K ", %8 row_newbcast:" #K " row_mask:0xf bank_mask:0xf\n\t"
+__device__ __forceinline__ void row_bcast8(float v, float (&out)[8]) {
+  __asm__("s_nop 1\n\t" QD_ROW_BCAST(0) QD_ROW_BCAST(1) QD_ROW_BCAST(2) QD_ROW_BCAST(3)
+              QD_ROW_BCAST(4) QD_ROW_BCAST(5) QD_ROW_BCAST(6) QD_ROW_BCAST(7)
+          : "=&v"(out[0]), "=&v"(out[1]), "=&v"(out[2]), "=&v"(out[3]), "=&v"(out[4]),
+            "=&v"(out[5]), "=&v"(out[6]), "=&v"(out[7])
+          : "v"(v));
 }
 
 // One rotation step of a row-wide minimum of (value, index) pairs, smaller
@@ -247,6 +302,16 @@ __device__ __forceinline__ float half_fold_sum(float v) {
   v = v + row_ror<2>(v);
   v = v + row_ror<1>(v);
   return v;
+}
+
+// Fold of 8 slices, lane l holding slice l / 8 of sum l mod 8: pairs of slices
+// four, two and one apart, the total in every lane.
+__device__ __forceinline__ float slice_fold_sum(float v) {
+  const auto h32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(h32[0]) + __uint_as_float(h32[1]);
+  const auto h16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(h16[0]) + __uint_as_float(h16[1]);
+  return v + row_ror<8>(v);
 }
 
 // The same fold for three values at once.  The first two steps pack values

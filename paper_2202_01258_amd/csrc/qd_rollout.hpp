@@ -5,9 +5,8 @@
 // s' = tanh(A s + B a).  Every individual has its own weights, so this is a
 // batch of independent GEMV chains, not one GEMM: no matrix core applies.
 //
-// One workgroup of H threads (H = hidden width, one or two waves) runs one
-// individual with all its weights in VGPRs for the whole episode.  The
-// summation order of every output is fixed (hidden layers and A s: four
+// One, two or eight waves run one individual with all its weights in VGPRs for
+// the whole episode.  The summation order of every output is fixed (hidden layers and A s: four
 // interleaved partial sums, then the bias; output layer: 8 slices folded
 // pairwise, then the bias; dynamics: A s + B a), which keeps the result
 // independent of the launch shape.
@@ -53,142 +52,131 @@ __device__ __forceinline__ float4 mlp_gene_block(const Params& p, const Pair& q,
   return make_genes<false>(p, q, g, j, 4 * blk);
 }
 
-// Makes the four genes opaque to the optimiser (an empty asm that claims to
-// change them): the prologue's genes are then finished where they are made,
-// instead of having the sampler's inputs carried into the episode loop where
-// the genes are first read, which needs several times the registers.
-__device__ __forceinline__ void settle(float4& v) {
-  __asm__ volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
-}
-
 // The layers' dot products: four interleaved partial sums (input k goes to
 // partial k mod 4, each an fma chain in input order from 0), folded as
-// (p0 + p2) + (p1 + p3) -- four independent dependency chains per lane.  The
-// inputs are broadcast from registers, not read from LDS one by one.
-// With the DPP control row_newbcast:m, the first source of v_fmac_f32 is
-// read from lane m of the executing lane's row of 16.  Component t of `v`
-// holds, in lane 16 r + m, input 4 m + t of a run of 64 inputs (the same in
-// every row r), so broadcast m of component t is input 4 m + t in every lane,
-// and each partial sum below still takes its inputs in ascending order.  One
-// float4 per lane per run replaces sixteen wave-wide LDS broadcasts.
-// The compiler does not fold a DPP move into v_fmac, hence the asm.  No VGPR
-// operand of a DPP instruction may be written by either of the two
-// instructions before it: every block opens with s_nop 1, and inside a block
-// each accumulator is written four instructions before it is read again.  The
-// blocks must run with every lane of the wave active.
-#define QD_BROW(B, W0, W1, W2, W3)                                                     \
-  "v_fmac_f32_dpp %0, %4, %" #W0 " row_newbcast:" #B " row_mask:0xf bank_mask:0xf\n\t" \
-  "v_fmac_f32_dpp %1, %5, %" #W1 " row_newbcast:" #B " row_mask:0xf bank_mask:0xf\n\t" \
-  "v_fmac_f32_dpp %2, %6, %" #W2 " row_newbcast:" #B " row_mask:0xf bank_mask:0xf\n\t" \
-  "v_fmac_f32_dpp %3, %7, %" #W3 " row_newbcast:" #B " row_mask:0xf bank_mask:0xf\n\t"
-#define QD_BROW3(B, W0, W1, W2)                                                        \
-  "v_fmac_f32_dpp %0, %4, %" #W0 " row_newbcast:" #B " row_mask:0xf bank_mask:0xf\n\t" \
-  "v_fmac_f32_dpp %1, %5, %" #W1 " row_newbcast:" #B " row_mask:0xf bank_mask:0xf\n\t" \
-  "v_fmac_f32_dpp %2, %6, %" #W2 " row_newbcast:" #B " row_mask:0xf bank_mask:0xf\n\t"
-#define QD_BFMA_IO(w)                                                                   \
-  : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3])                             \
-  : "v"(v.x), "v"(v.y), "v"(v.z), "v"(v.w), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), \
-    "v"(w[4]), "v"(w[5]), "v"(w[6]), "v"(w[7]), "v"(w[8]), "v"(w[9]), "v"(w[10])
-#define QD_BFMA_IO16(w)                                                                 \
-  QD_BFMA_IO(w), "v"(w[11]), "v"(w[12]), "v"(w[13]), "v"(w[14]), "v"(w[15])
+// (p0 + p2) + (p1 + p3).
+//
+// A quad of lanes shares R rows (neurons) of a layer and lane t of the quad
+// runs partial t of every one of them, so a lane needs the inputs 4 m + t
+// only: N / 4 of the N inputs, read once and used for R rows.  With the inputs
+// in LDS as [t][m], a float4 read serves 4 R fmas -- plain v_fmac on vector
+// registers, which the SIMD issues two at a time, where a broadcast inside the
+// instruction (DPP) or a scalar operand is issued one at a time.
+// Accumulator r of lane t belongs to row r ^ (t mod R) of the quad: with that
+// order the fold needs no select, and (for R = 4) lane t ends with row t.
+template <int CTRL>
+__device__ __forceinline__ float quad_perm(float v) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float quad_xor1(float v) { return quad_perm<0xb1>(v); }   // [1,0,3,2]
+__device__ __forceinline__ float quad_xor2(float v) { return quad_perm<0x4e>(v); }   // [2,3,0,1]
 
-// Inputs 16 B .. 16 B + 15 of a run (broadcasts 4 B .. 4 B + 3), weights w[0 .. 16).
-template <int B>
-__device__ __forceinline__ void bfma16(float (&acc)[4], const float4& v, const float* w) {
-  if constexpr (B == 0) {
-    __asm__("s_nop 1\n\t" QD_BROW(0, 8, 9, 10, 11) QD_BROW(1, 12, 13, 14, 15)
-                QD_BROW(2, 16, 17, 18, 19) QD_BROW(3, 20, 21, 22, 23) QD_BFMA_IO16(w));
-  } else if constexpr (B == 1) {
-    __asm__("s_nop 1\n\t" QD_BROW(4, 8, 9, 10, 11) QD_BROW(5, 12, 13, 14, 15)
-                QD_BROW(6, 16, 17, 18, 19) QD_BROW(7, 20, 21, 22, 23) QD_BFMA_IO16(w));
-  } else if constexpr (B == 2) {
-    __asm__("s_nop 1\n\t" QD_BROW(8, 8, 9, 10, 11) QD_BROW(9, 12, 13, 14, 15)
-                QD_BROW(10, 16, 17, 18, 19) QD_BROW(11, 20, 21, 22, 23) QD_BFMA_IO16(w));
+// Sum of the row that lane t of a quad ends with: row t (R = 4), row t mod 2
+// (R = 2), the quad's row (R = 1).  Each addition is one of (p0 + p2) + (p1 + p3)
+// up to the order of its two operands.
+template <int R>
+__device__ __forceinline__ float quad_fold(const float (&acc)[R]) {
+  static_assert(R == 1 || R == 2 || R == 4, "rows per quad");
+  if constexpr (R == 4) {
+    const float b0 = acc[0] + quad_xor2(acc[2]), b1 = acc[1] + quad_xor2(acc[3]);
+    return b0 + quad_xor1(b1);
+  } else if constexpr (R == 2) {
+    const float b0 = acc[0] + quad_xor2(acc[0]), b1 = acc[1] + quad_xor2(acc[1]);
+    return b0 + quad_xor1(b1);
   } else {
-    static_assert(B == 3, "four blocks per run");
-    __asm__("s_nop 1\n\t" QD_BROW(12, 8, 9, 10, 11) QD_BROW(13, 12, 13, 14, 15)
-                QD_BROW(14, 16, 17, 18, 19) QD_BROW(15, 20, 21, 22, 23) QD_BFMA_IO16(w));
+    const float b0 = acc[0] + quad_xor2(acc[0]);
+    return b0 + quad_xor1(b0);
   }
 }
 
-// Inputs 16 .. 26 of a run (broadcasts 4, 5 and 6 without input 27), weights w[0 .. 11).
-__device__ __forceinline__ void bfma11(float (&acc)[4], const float4& v, const float* w) {
-  __asm__("s_nop 1\n\t" QD_BROW(4, 8, 9, 10, 11) QD_BROW(5, 12, 13, 14, 15)
-              QD_BROW3(6, 16, 17, 18) QD_BFMA_IO(w));
+// The T at byte offset `at` (a lane's own, in one register) from p (the same in
+// every lane, folded into the instruction).
+template <class T>
+__device__ __forceinline__ const T& lds_at(const float* p, int at) {
+  return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + at);
 }
 
-// That dot product for N a multiple of 64; run r of x is read as one float4 per lane
-// from x + 64 r + 4 (lane mod 16), 16-byte aligned.
-template <int N>
-__device__ __forceinline__ float dot4_bcast(const float* w, const float* x) {
-  static_assert(N % 64 == 0, "whole runs of 64 inputs");
-  const int m = (int)(threadIdx.x & 15);
-  float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+__device__ __forceinline__ float& lds_ref(float* p, int at) {
+  return *reinterpret_cast<float*>(reinterpret_cast<char*>(p) + at);
+}
+
+// M inputs of this lane's partial for R rows, weights w[r][m]; x: the lane's
+// [t] row, 16-byte aligned.  LIM inputs' reads are in flight at most.
+template <int R, int M, int LIM>
+__device__ __forceinline__ float quad_dot(const float (&w)[R][M], const float* x, int at) {
+  float acc[R];
 #pragma unroll
-  for (int r = 0; r < N / 64; ++r) {
-    const float4 v = *reinterpret_cast<const float4*>(x + 64 * r + 4 * m);
-    bfma16<0>(acc, v, w + 64 * r);
-    bfma16<1>(acc, v, w + 64 * r + 16);
-    bfma16<2>(acc, v, w + 64 * r + 32);
-    bfma16<3>(acc, v, w + 64 * r + 48);
-  }
-  return (acc[0] + acc[2]) + (acc[1] + acc[3]);
-}
-
-// That dot product for N = 27 on `v`, the float4 a lane reads from x + 4 (lane mod 8) of a
-// 32-float, 16-byte aligned x (its input 27 and broadcast 7 are never used).
-__device__ __forceinline__ float dot4_bcast27(const float* w, const float4& v) {
-  float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  bfma16<0>(acc, v, w);
-  bfma11(acc, v, w + 16);
-  return (acc[0] + acc[2]) + (acc[1] + acc[3]);
-}
-
-__device__ __forceinline__ float pick4(const float4& v, int k) {
-  return k == 0 ? v.x : (k == 1 ? v.y : (k == 2 ? v.z : v.w));
-}
-
-// Fills dst[0 .. LEN) with genes first .. first+LEN-1, first a multiple of 4.
-template <bool GEN0, int LEN>
-__device__ __forceinline__ void mlp_genes_aligned(const Params& p, const Pair& q, uint32_t g,
-                                                  int j, int first, float* dst) {
-  static_assert(LEN % 4 == 0, "aligned runs hold whole gene blocks");
+  for (int r = 0; r < R; ++r) acc[r] = 0.0f;
 #pragma unroll
-  for (int t4 = 0; t4 < LEN / 4; ++t4) {
-    float4 v = mlp_gene_block<GEN0>(p, q, g, j, (first >> 2) + t4);
-    settle(v);
-    dst[4 * t4] = v.x;
-    dst[4 * t4 + 1] = v.y;
-    dst[4 * t4 + 2] = v.z;
-    dst[4 * t4 + 3] = v.w;
-  }
-}
-
-// Fills dst[0 .. LEN) with genes first .. first+LEN-1 (any alignment).
-template <bool GEN0, int LEN>
-__device__ __forceinline__ void mlp_genes_run(const Params& p, const Pair& q, uint32_t g, int j,
-                                              int first, float* dst) {
-  const int b0 = first >> 2, b1 = (first + LEN - 1) >> 2;
-  for (int blk = b0; blk <= b1; ++blk) {
-    float4 v = mlp_gene_block<GEN0>(p, q, g, j, blk);
-    settle(v);
+  for (int m4 = 0; m4 < M; m4 += 4) {
+    const float4 v = lds_at<float4>(x + m4, at);
+    const float xv[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-    for (int t = 0; t < LEN; ++t) {
-      const int gi = first + t;
-      if ((gi >> 2) == blk) dst[t] = pick4(v, gi & 3);
+    for (int i = 0; i < 4; ++i) {
+      if (m4 + i < M) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[r] = fma32(w[r][m4 + i], xv[i], acc[r]);
+      }
+    }
+    if (m4 % LIM == LIM - 4 && m4 + 4 < M) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) __asm__ volatile("" : "+v"(at), "+v"(acc[r]));
     }
   }
+  return quad_fold<R>(acc);
+}
+
+// The same with the inputs already in registers.
+template <int R, int M>
+__device__ __forceinline__ float quad_dot(const float (&w)[R][M], const float4 (&x)[(M + 3) / 4]) {
+  float acc[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) acc[r] = 0.0f;
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    const float4& v = x[m / 4];
+    const float xm = m % 4 == 0 ? v.x : (m % 4 == 1 ? v.y : (m % 4 == 2 ? v.z : v.w));
+#pragma unroll
+    for (int r = 0; r < R; ++r) acc[r] = fma32(w[r][m], xm, acc[r]);
+  }
+  return quad_fold<R>(acc);
+}
+
+// Orders the LDS accesses of one wave's lanes around this point.  A wave's LDS
+// instructions execute in program order, so the compiler's order is all it
+// takes: no wait for a write before the reads that follow it.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Keeps a value in a register of its own (an empty asm that claims to change
+// it): the optimiser no longer derives other registers from how it was made.
+template <class T>
+__device__ __forceinline__ void hold(T& v) { __asm__ volatile("" : "+v"(v)); }
+
+// A pair that is the same in every lane of the wave, moved to scalar registers.
+__device__ __forceinline__ Pair uniform_pair(const Params& p, const Pair& v) {
+  Pair q = v;
+  q.c1 = __builtin_amdgcn_readfirstlane(v.c1);
+  q.c2 = __builtin_amdgcn_readfirstlane(v.c2);
+  q.banks = (uint32_t)__builtin_amdgcn_readfirstlane((int)v.banks);
+  q.lambda = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v.lambda)));
+  q.row1 = geno_row(p, q.banks & 1u, q.c1);
+  q.row2 = geno_row(p, (q.banks >> 1) & 1u, q.c2);
+  return q;
+}
+
+// Orders the LDS accesses of one individual's NT threads around this point.
+template <int NT>
+__device__ __forceinline__ void group_sync() {
+  if constexpr (NT > 64) __syncthreads();
+  else wave_sync();
 }
 
 // Steps a rollout records for its reward and descriptor sums (see k_rollout).
 constexpr int kRing = 64;
-
-// Orders the LDS accesses of one wave's lanes around this point.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-}
 
 // Folds the first m ring slots into the running sums; called by all 64
 // lanes of the output wave (o: lane index in it).  Lane i < m turns slot i
@@ -213,6 +201,7 @@ __device__ __forceinline__ void flush_ring(float (*ra)[A], float (*rs)[kRing + 1
   if (o <= 4) {
     const float* row = rs[o];
     int i = 0;
+#pragma unroll 1
     for (; i + 8 <= m; i += 8) {   // eight loads in flight, then eight adds
       float v[8];
 #pragma unroll
@@ -220,170 +209,324 @@ __device__ __forceinline__ void flush_ring(float (*ra)[A], float (*rs)[kRing + 1
 #pragma unroll
       for (int t = 0; t < 8; ++t) acc = acc + v[t];
     }
+#pragma unroll 1
     for (; i < m; ++i) acc = acc + row[i];
   }
   wave_sync();
 }
 
-// One individual per workgroup of H threads (H / 64 waves):
-//   thread o      row o of W1 and W2, b1[o], b2[o] in VGPRs; hidden neuron o
-//   output wave   the last wave.  Its 64 lanes (o3 = lane / 8, slice = lane %
-//                 8) hold W3[o3][slice of H/8 inputs]; the 8 partial sums of an
-//                 action are folded inside its group of 8 lanes.  Its lanes
-//                 i < 27 also hold row i of A and B (shared environment) and
-//                 compute state component i.
-// Per step: layer 1 (and A s on the output wave), barrier, layer 2, barrier,
-// then on the output wave alone the output layer, B a (the actions broadcast
-// by readlane) and the new state, barrier.  The reward and the descriptor's
-// sigmoids, which only lanes 0 .. 4 of the output wave need, are not
-// evaluated in the step: the step's actions and new-state components 0 .. 4
-// go to a ring in LDS, folded in every kRing steps by the output wave.
-template <int H, bool GEN0, bool KEEP>
-__global__ __launch_bounds__(H, H == 64 ? 3 : 2) void k_rollout(const Params p, uint32_t g) {
-  constexpr int O = kObs, A = kAct, SL = H / 8;
-  constexpr int E1 = H * O, E2 = E1 + H, E3 = E2 + H * H, E4 = E3 + H;   // W3 at E4, b3 after
-  constexpr int OUT_WAVE_FIRST = H - 64;                                  // first lane of it
-  __shared__ __attribute__((aligned(16))) float s_state[2][32];
-  __shared__ __attribute__((aligned(16))) float s_h1[H];
-  __shared__ float s_h2[H];
-  // Ring of the last kRing valid steps: their actions, and their new states'
-  // components 0 .. 4 (later the step's reward and four sigmoids).  Rows are
-  // padded so that lanes 0 .. 4 reading one column hit different banks.
-  __shared__ __attribute__((aligned(16))) float s_ra[kRing][A];
-  __shared__ float s_rs[5][kRing + 1];
-  __shared__ int s_fail;
+// One individual per W waves.  Quad u = 16 wave + lane / 4 of its waves holds
+// rows R u .. R u + R - 1 of W1 and W2, R = H / (16 W), each lane its partial's
+// weights (inputs t, t + 4, ...) of those rows in VGPRs for the whole episode.
+// In the last stage of a step lane l holds W3[l mod 8][slice l / 8 of H / 8
+// inputs], whose 8 partial sums are folded across the wave, and works on state
+// component 2 (l / 4) + (l mod 2) of the new state with that row of B and two
+// rows of A (a quad's two state components).
+// Per step: layer 1, barrier, layer 2 (and A s, on the other wave than the
+// output one), barrier, then on the output wave the output layer, B a and the
+// new state, barrier.  With one wave there is no barrier, and with one row per
+// quad (R = 1: few individuals, every SIMD has waves to spare) each wave runs
+// the last stage for itself, which saves the third one.  The reward and the
+// descriptor's sigmoids, which only five lanes need, are not evaluated in the
+// step: its actions and new-state components 0 .. 4 go to a ring in LDS, folded
+// in every kRing steps by the output wave.
+//
+// What bounds a step is the length of its chain: a lone wave issues one
+// instruction per ~5.3 cycles, and every exchange through LDS adds its latency
+// (the state is read into registers as soon as it is written, and A s fills the
+// wait for the first layer).  At three waves per SIMD (64 wide) the SIMD issues
+// one VALU instruction per ~3 cycles, 280 a step.  Measured, one generation
+// with the earlier layout (inputs broadcast inside DPP fmas, a row per lane)
+// and this one: 64 wide, T = 250: 256 individuals 228 -> 200 us, 8192: 860 ->
+// 762 us (36.6 -> 41.3 TFLOP/s); 128 wide, T = 400: 256: 448 -> 410 us, 1501:
+// 1052 -> 928 us, 16384: 8165 -> 7420 us.
+template <int H, int W>
+struct RolloutShape {
+  static constexpr int O = kObs, A = kAct, NT = W * 64, R = H / (16 * W);
+  // individuals per workgroup: two one-wave individuals share the sampler's
+  // table, so that the LDS of a CU holds the 12 that its registers hold
+  static constexpr int kInd = W == 1 ? 2 : 1, kThreads = NT * kInd;
+  static constexpr int kWavesPerSimd = W == 1 ? 3 : (W == 2 ? 2 : 4);
+  static constexpr bool kOwnState = R == 1 && W > 1;     // every wave runs the last stage
+  static constexpr bool kShared = W > 1 && !kOwnState;   // the output wave runs it for all
+  static constexpr int kSlab = W == 1 ? 8 : 16;          // inputs of W2 per pass of the prologue
+  static constexpr int kSlabPitch = kSlab + 4;
+  // A vector of N inputs lies in LDS as [t][m], input 4 m + t, rows kPitch
+  // apart (padded: the four rows' float4 reads fall in different banks).
+  static constexpr int kPitch = H / 4 + 4;
+  // The workgroup's LDS in floats: the sampler's table, then per individual the
+  // prologue's stage, later the episode's buffers.
+  static constexpr int kTab = kNormalRows * 4;
+  static constexpr int kRa = 0, kRs = kRa + kRing * A, kX = kRs + (5 * (kRing + 1) + 3) / 4 * 4;
+  static constexpr int kXs = kPitch * 4, kH1 = kX + kXs * (kOwnState ? W : 1), kH2 = kH1 + kXs;
+  static constexpr int kAs = kH2 + kXs, kFail = kAs + (kShared ? 32 : 0);
+  static constexpr int kEpisode = kFail + (kShared ? 4 : 0);
+  static constexpr int kW1Stage = H * O, kW2Stage = H * kSlabPitch, kTail = 9 * H + A;
+  // Registers beside W1 and W2: the output wave's slice of W3 and row of B, and
+  // A's rows on the wave that works out A s -- the same registers where these
+  // are different waves.
+  static constexpr int kAuxB = 0, kAuxB3 = A, kAuxW3 = A + 1;
+  static constexpr int kLast = kAuxW3 + H / 8, kAuxA = kShared ? 0 : kLast;
+  static constexpr int max2(int a, int b) { return a > b ? a : b; }
+  static constexpr int kAux = max2(kAuxA + 14, kLast);
+  static constexpr int kRegion = max2(max2(kEpisode, kW1Stage), max2(kW2Stage, kTail + H));
+  static constexpr int kMem = kTab + kInd * kRegion;
+};
 
-  __shared__ float4 s_ntab[kNormalRows];
+template <int H, int W, bool GEN0, bool KEEP>
+__device__ __forceinline__ void rollout(const Params& p, uint32_t g) {
+  using S = RolloutShape<H, W>;
+  constexpr int O = S::O, A = S::A, R = S::R, NT = S::NT, SL = H / 8, M1 = (O + 3) / 4, M2 = H / 4;
+  constexpr int P = S::kPitch;
+  constexpr int E1 = H * O, E2 = E1 + H, E3 = E2 + H * H;   // b1, W2, b2 (then W3, b3)
+  static_assert(O == 27 && A == 8, "lane order of the state and the actions");
+  __shared__ __attribute__((aligned(16))) float s_mem[S::kMem];
+  float4* s_tab = reinterpret_cast<float4*>(s_mem);
 
-  const int o = threadIdx.x;
-  const int j = blockIdx.x;
+  const int tid = threadIdx.x & (NT - 1), lane = threadIdx.x & 63;
+  const int ind = S::kInd == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / NT);
+  const int wave = W == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int t = lane & 3, quad = wave * 16 + (lane >> 2);
+  const int row0 = quad * R, flip = t & (R - 1);
+  // the last workgroup's spare wave repeats the last individual and stores nothing
+  const int jj = (int)blockIdx.x * S::kInd + ind;
+  const bool mine = jj < p.nb;
+  const int j = mine ? jj : p.nb - 1;
+  float* st = s_mem + S::kTab + ind * S::kRegion;
+  // Row rho of the R u + r counts neuron 4 (rho mod H/4) + rho / (H/4): the
+  // order of the [t][m] layout, so a lane's place in it follows from its lane.
+  const auto neuron = [](int rho) { return 4 * (rho & (M2 - 1)) + rho / M2; };
+  // The output wave keeps the ring.  Where it runs the last stage for both
+  // waves, the other one works out A s for it, and which of the two it is
+  // alternates with every 256 workgroups (about one per CU), so that the SIMDs
+  // of a CU share that work.
+  const int out_wave = S::kShared ? (int)((blockIdx.x >> 8) & 1u) : W - 1;
+  const bool is_out = wave == out_wave;
+  const bool is_last = !S::kShared || is_out, is_as = !S::kShared || !is_out;
 
   Pair q{nullptr, nullptr, 0.0f, -1, -1, 0u};
   if (!GEN0) {
     const int nocc = p.counters[0];
     if (nocc <= 0) {
-      if (o == 0) record_empty_archive(p, j);
+      if (tid == 0 && mine) record_empty_archive(p, j);
       return;
     }
-    stage_normal_table(s_ntab, p.ntab, o, H);
+    stage_normal_table(s_tab, p.ntab, (int)threadIdx.x, NT * S::kInd);
     __syncthreads();
-    q = select_pair(p, g, j, nocc, Tables{s_ntab});
+    q = uniform_pair(p, select_pair(p, g, j, nocc, Tables{s_tab}));
   }
 
-  // ---- prologue: this individual's genotype, straight into registers
-  const bool out_lane = o >= OUT_WAVE_FIRST;
-  const int ol = o - OUT_WAVE_FIRST, o3 = (ol >> 3) & 7, slice = ol & 7;
-  const bool dyn_lane = out_lane && ol < O;   // holds state component ol
-  float w1[O], w2[H], w3[SL], arow[O], brow[A];
-  float b1v, b2v, b3v = 0.0f;
-  mlp_genes_run<GEN0, O>(p, q, g, j, o * O, w1);
-  mlp_genes_aligned<GEN0, H>(p, q, g, j, E2 + o * H, w2);   // E2 = 28 H
-  {
-    float t[1];
-    mlp_genes_run<GEN0, 1>(p, q, g, j, E1 + o, t);
-    b1v = t[0];
-    mlp_genes_run<GEN0, 1>(p, q, g, j, E3 + o, t);
-    b2v = t[0];
-    if (out_lane) {
-      mlp_genes_run<GEN0, 1>(p, q, g, j, E4 + A * H + o3, t);
-      b3v = t[0];
+  // ---- prologue: this individual's genotype, through LDS into registers.  Its
+  // gene blocks are made by all its threads; W1 comes last, so that the fewest
+  // weights are in registers beside the sampler's.
+  const auto make = [&](int blk, float* dst) {
+    const float4 v = mlp_gene_block<GEN0>(p, q, g, j, blk);
+    *reinterpret_cast<float4*>(dst) = v;
+    if (KEEP && mine) *reinterpret_cast<float4*>(p.off_geno + (size_t)j * (size_t)p.stride + 4 * blk) = v;
+  };
+  float w1[R][M1], w2[R][M2], aux[S::kAux];
+  // W2, kSlab inputs of every row a pass
+#pragma unroll
+  for (int m0 = 0; m0 < M2; m0 += S::kSlab / 4) {
+    constexpr int BR = S::kSlab / 4;
+#pragma unroll 1
+    for (int b = tid; b < H * BR; b += NT) {
+      const int row = b / BR, m = b % BR;
+      make((E2 + row * H) / 4 + m0 + m, st + row * S::kSlabPitch + 4 * m);
+    }
+    group_sync<NT>();
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int m = 0; m < BR; ++m) {
+        w2[r][m0 + m] = st[neuron(row0 + (r ^ flip)) * S::kSlabPitch + 4 * m + t];
+        hold(w2[r][m0 + m]);
+      }
+    group_sync<NT>();
+  }
+  // b2, W3, b3, and b1
+#pragma unroll 1
+  for (int b = tid; b < (S::kTail + H) / 4; b += NT)
+    make(b < S::kTail / 4 ? E3 / 4 + b : E1 / 4 + b - S::kTail / 4, st + 4 * b);
+  group_sync<NT>();
+  const float b1 = st[S::kTail + neuron(row0 + flip)], b2 = st[neuron(row0 + flip)];
+  if (is_last) {
+#pragma unroll
+    for (int i = 0; i < SL; ++i) aux[S::kAuxW3 + i] = st[H + (lane & 7) * H + (lane >> 3) * SL + i];
+    aux[S::kAuxB3] = st[9 * H + (lane & 7)];
+  }
+  group_sync<NT>();
+#pragma unroll 1
+  for (int b = tid; b < H * O / 4; b += NT) make(b, st + 4 * b);
+  group_sync<NT>();
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    // input 27 does not exist: -0 times the zero in the state's place 27 adds nothing
+#pragma unroll
+    for (int m = 0; m < M1; ++m) {
+      w1[r][m] = 4 * m + t < O ? st[neuron(row0 + (r ^ flip)) * O + 4 * m + t] : -0.0f;
+      hold(w1[r][m]);
     }
   }
-  if (out_lane) mlp_genes_aligned<GEN0, SL>(p, q, g, j, E4 + o3 * H + slice * SL, w3);
-  if (KEEP) {
-    float* row = p.off_geno + (size_t)j * (size_t)p.stride;
-    for (int t = 0; t < O; ++t) row[o * O + t] = w1[t];
-    for (int t = 0; t < H; ++t) row[E2 + o * H + t] = w2[t];
-    row[E1 + o] = b1v;
-    row[E3 + o] = b2v;
-    if (out_lane) {
-      for (int t = 0; t < SL; ++t) row[E4 + o3 * H + slice * SL + t] = w3[t];
-      if (slice == 0) row[E4 + A * H + o3] = b3v;
-    }
-  }
+  group_sync<NT>();   // every stage is free
+
+  // ---- A, B and the first state
+  const int srow = 2 * (lane >> 2) + (lane & 1);   // state component this lane works on
+  const bool dyn_lane = srow < O && (lane & 2) == 0;
   const float* envA = p.env;
   const float* envB = p.env + O * O;
   const float* envS = p.env + O * O + O * A;
+  // (A's entry 27 of a row is the next row's first, or B's: read and dropped)
+  if (is_last) {
+    const float* src = envB + (srow < O ? srow : 0) * A;
 #pragma unroll
-  for (int k = 0; k < O; ++k) arow[k] = 0.0f;
-  if (dyn_lane) {
-#pragma unroll
-    for (int k = 0; k < O; ++k) arow[k] = envA[ol * O + k];
-#pragma unroll
-    for (int k = 0; k < A; ++k) brow[k] = envB[ol * A + k];
-    s_state[0][ol] = envS[ol];
+    for (int k = 0; k < A; ++k) aux[S::kAuxB + k] = srow < O ? src[k] : 0.0f;
   }
-  if (o == 0) s_fail = 0;
-  __syncthreads();
+  if (is_as) {
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const int row = 2 * (lane >> 2) + (r ^ (lane & 1));
+      const float* src = envA + (row < O ? row : 0) * O + t;
+#pragma unroll
+      for (int m = 0; m < M1; ++m) {
+        const float v = src[4 * m];
+        aux[S::kAuxA + M1 * r + m] = 4 * m + t >= O ? -0.0f : (row < O ? v : 0.0f);
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < S::kAux; ++i) hold(aux[i]);
+  float (*s_ra)[A] = reinterpret_cast<float (*)[A]>(st + S::kRa);
+  float (*s_rs)[kRing + 1] = reinterpret_cast<float (*)[kRing + 1]>(st + S::kRs);
+  float* s_x = st + S::kX + (S::kOwnState ? S::kXs * wave : 0);
+  float* s_h1 = st + S::kH1;
+  float* s_h2 = st + S::kH2;
+  float* s_as = st + S::kAs;
+  int* s_fail = reinterpret_cast<int*>(st + S::kFail);
+  if (lane < 32) {   // places 27 .. 31 of the state stay zero
+    const int i = 4 * (lane & 7) + (lane >> 3);
+    s_x[(lane >> 3) * P + (lane & 7)] = i < O ? envS[i] : 0.0f;
+  }
+  if (S::kShared && tid == 0) *s_fail = 0;
+  group_sync<NT>();
 
   // ---- episode; with death_mode != 0 it ends at the first new state whose
   // component 0 is below death_below, and that step counts for nothing.
   // Output-wave lane 0 sums the rewards, lanes 1 .. 4 the sigmoids of state
   // components 1 .. 4, each in step order; both are worked out from the ring,
   // kRing steps at a time (flush_ring), not inside the step.
+  // The lane's offsets, kept in one register each: every LDS address in the
+  // step is one of them plus a constant.
+  int at_part = 4 * t * P;
+  int at_row = 4 * ((row0 + flip) + 4 * ((row0 + flip) / M2));
+  int at_slice = (lane >> 3) * SL, at_srow = 4 * ((srow & 3) * P + (srow >> 2));
+  hold(at_part);
+  hold(at_row);
+  hold(at_slice);
+  hold(at_srow);
+  float4 x[2];   // this lane's partial of the state
+  const auto read_state = [&]() {
+    x[0] = lds_at<float4>(s_x, at_part);
+    x[1] = lds_at<float4>(s_x + 4, at_part);
+  };
+  const auto a_times_s = [&]() {
+    float w[2][M1];
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+      for (int m = 0; m < M1; ++m) w[r][m] = aux[S::kAuxA + M1 * r + m];
+    return quad_dot<2, M1>(w, x);
+  };
   float acc = 0.0f;
-  int cur = 0, valid = 0;
+  int valid = 0;
+  bool failed = false;
+  read_state();
   for (int step = 0; step < p.T; ++step) {
     const int slot = valid & (kRing - 1);
-    static_assert(O == 27, "the state is read as broadcasts 0 .. 6 of one float4");
-    const float4 sv = *reinterpret_cast<const float4*>(&s_state[cur][4 * (o & 7)]);
-    const float z1 = dot4_bcast27(w1, sv) + b1v;
+    const float z1 = quad_dot<R, M1>(w1, x) + b1;
+    lds_ref(s_h1, at_row) = tanh32(z1);
     float as = 0.0f;
-    if (out_lane) as = dot4_bcast27(arow, sv);   // the whole output wave (dyn_lane uses it)
-    s_h1[o] = tanh32(z1);
-    __syncthreads();
-    const float z2 = dot4_bcast<H>(w2, s_h1) + b2v;
-    s_h2[o] = tanh32(z2);
-    __syncthreads();
-    if (out_lane) {
+    if (!S::kShared) as = a_times_s();
+    group_sync<NT>();
+    const float z2 = quad_dot<R, M2, W == 8 ? 16 : 32>(w2, s_h1, at_part) + b2;
+    lds_ref(s_h2, at_row) = tanh32(z2);
+    if (S::kShared && is_as) s_as[srow] = a_times_s();
+    group_sync<NT>();
+    if (is_last) {
+      // inputs SL s + i of slice s, at place (i mod 4, SL s / 4 + i / 4)
+      float h2[SL];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        typedef float run __attribute__((ext_vector_type(SL / 4)));
+        const run v = lds_at<run>(s_h2 + c * P, at_slice);
+#pragma unroll
+        for (int i = 0; i < SL / 4; ++i) h2[4 * i + c] = v[i];
+      }
       float pa = 0.0f;
 #pragma unroll
-      for (int t = 0; t < SL; ++t) pa = fma32(w3[t], s_h2[slice * SL + t], pa);
-      pa = pa + row_shl<4>(pa);   // slices s and s + 4 (groups of 8 never straddle a row)
-      pa = pa + row_shl<2>(pa);   // then s + 2
-      pa = pa + row_shl<1>(pa);   // then s + 1
-      const float act = tanh32(pa + b3v);   // action o3 in lane 8 o3 (slice 0)
-      if (slice == 0) s_ra[slot][o3] = act;
-      float ak[A];
+      for (int i = 0; i < SL; ++i) pa = fma32(aux[S::kAuxW3 + i], h2[i], pa);
+      pa = slice_fold_sum(pa);
+      const float a = tanh32(pa + aux[S::kAuxB3]);             // action lane mod 8
+      if (is_out && lane < A) s_ra[slot][lane] = a;
+      // every row of 16 lanes holds all the actions, action k in its lane k
+      float ak[A], ba = 0.0f;
+      row_bcast8(a, ak);
 #pragma unroll
-      for (int k = 0; k < A; ++k)
-        ak[k] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(act), 8 * k));
-      if (dyn_lane) {
-        float ba = 0.0f;
-#pragma unroll
-        for (int k = 0; k < A; ++k) ba = fma32(brow[k], ak[k], ba);
-        const float sn = tanh32(as + ba);
-        s_state[cur ^ 1][ol] = sn;
-        // lane 0 of this wave holds component 0 of the new state
-        const bool fail = p.death_mode != 0 &&
-                          __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(sn), 0)) <
-                              p.death_below;
-        if (fail) {
-          if (ol == 0) s_fail = 1;
-        } else if (ol <= 4) {
-          s_rs[ol][slot] = sn;
-        }
+      for (int k = 0; k < A; ++k) ba = fma32(aux[S::kAuxB + k], ak[k], ba);
+      if (S::kShared) as = s_as[srow];
+      const float sn = tanh32(as + ba);
+      if (dyn_lane) lds_ref(s_x, at_srow) = sn;
+      // lane 0 holds component 0 of the new state
+      failed = p.death_mode != 0 &&
+               __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(sn), 0)) < p.death_below;
+      if (failed) {
+        if (S::kShared && lane == 0) *s_fail = 1;
+      } else if (is_out && dyn_lane && srow <= 4) {
+        s_rs[srow][slot] = sn;
       }
     }
-    cur ^= 1;
-    __syncthreads();
-    if (s_fail) break;   // the same value in every thread after the barrier
+    if (S::kShared) {
+      __syncthreads();
+      read_state();
+      failed = *s_fail != 0;   // the same value in every thread after the barrier
+    } else {
+      wave_sync();
+      read_state();
+    }
+    if (failed) break;
     ++valid;
     // a full ring: the output wave, its only writer, folds it in
-    if ((valid & (kRing - 1)) == 0 && out_lane) flush_ring<A>(s_ra, s_rs, kRing, ol, acc);
+    if ((valid & (kRing - 1)) == 0 && is_out) flush_ring<A>(s_ra, s_rs, kRing, lane, acc);
   }
-  if (out_lane) flush_ring<A>(s_ra, s_rs, valid & (kRing - 1), ol, acc);
+  if (!is_out || !mine) return;
+  flush_ring<A>(s_ra, s_rs, valid & (kRing - 1), lane, acc);
   // death flag (Appendix A.4 i): a NaN objective is never inserted
-  const bool dead = (p.death_mode == 2 && s_fail) || valid == 0;
-  if (out_lane && ol == 0) {
+  const bool dead = (p.death_mode == 2 && failed) || valid == 0;
+  if (lane == 0) {
     p.off_fit[j] = dead ? __builtin_nanf("") : acc;
     p.off_par[2 * j] = q.c1;
     p.off_par[2 * j + 1] = q.c2;
     p.off_bank[j] = (uint8_t)q.banks;
     p.off_won[j] = 0;
-  } else if (out_lane && ol <= 4) {
-    p.off_desc[(size_t)j * 4 + (ol - 1)] = valid > 0 ? acc / (float)valid : 0.0f;
+  } else if (lane <= 4) {
+    p.off_desc[(size_t)j * 4 + (lane - 1)] = valid > 0 ? acc / (float)valid : 0.0f;
   }
+}
+
+constexpr int rollout_waves(int hid) { return hid / 64; }
+
+template <int H, bool GEN0, bool KEEP>
+__global__ __launch_bounds__((RolloutShape<H, rollout_waves(H)>::kThreads),
+                             (RolloutShape<H, rollout_waves(H)>::kWavesPerSimd))
+void k_rollout(const Params p, uint32_t g) {
+  rollout<H, rollout_waves(H), GEN0, KEEP>(p, g);
+}
+
+// The 128-wide policies of a batch of at most one individual per CU.
+template <bool GEN0, bool KEEP>
+__global__ __launch_bounds__((RolloutShape<128, 8>::kThreads), (RolloutShape<128, 8>::kWavesPerSimd))
+void k_rollout_few(const Params p, uint32_t g) {
+  rollout<128, 8, GEN0, KEEP>(p, g);
 }
 
 // Winners of a policy batch: a workgroup takes kRegenCellsMlp consecutive
@@ -430,22 +573,43 @@ __global__ __launch_bounds__(256) void k_regen_mlp(const Params p, uint32_t g) {
 }
 
 // Launchers: `go(kernel, grid, block, args...)` makes the launch.
+// Waves per individual.  64 wide: one (two or four shorten the layers by less
+// than their barriers cost: 230 and 199 us against 200 us for 64 to 256
+// individuals and 250 steps, 239 and 340 us against 239 us for 1024).  128
+// wide: two, whose weights leave room for two waves per SIMD, or eight of one
+// row per quad while there is at most one individual per CU (64 to 256
+// individuals, 400 steps: 410 us against 436 us; 512: 590 against 470 us).
+constexpr int kEightWaveBatch = 256;
+
+template <int H, class Go>
+inline void launch_rollout_as(const Params& p, bool gen0, uint32_t g, bool keep, const Go& go) {
+  using S = RolloutShape<H, rollout_waves(H)>;
+  const dim3 grid((unsigned)((p.nb + S::kInd - 1) / S::kInd)), block(S::kThreads);
+  if (gen0) {
+    if (keep) go(k_rollout<H, true, true>, grid, block, p, g);
+    else go(k_rollout<H, true, false>, grid, block, p, g);
+  } else {
+    if (keep) go(k_rollout<H, false, true>, grid, block, p, g);
+    else go(k_rollout<H, false, false>, grid, block, p, g);
+  }
+}
+
 template <class Go>
 inline void launch_rollout(const Params& p, bool gen0, uint32_t g, bool keep, const Go& go) {
-  const dim3 grid((unsigned)p.nb);
-#define QD_RO(H)                                                        \
-  do {                                                                  \
-    if (gen0) {                                                         \
-      if (keep) go(k_rollout<H, true, true>, grid, dim3(H), p, g);      \
-      else go(k_rollout<H, true, false>, grid, dim3(H), p, g);          \
-    } else {                                                            \
-      if (keep) go(k_rollout<H, false, true>, grid, dim3(H), p, g);     \
-      else go(k_rollout<H, false, false>, grid, dim3(H), p, g);         \
-    }                                                                   \
-  } while (0)
-  if (p.hid == 64) QD_RO(64);
-  else QD_RO(128);
-#undef QD_RO
+  if (p.hid == 64) {
+    launch_rollout_as<64>(p, gen0, g, keep, go);
+  } else if (p.nb > kEightWaveBatch) {
+    launch_rollout_as<128>(p, gen0, g, keep, go);
+  } else {
+    const dim3 grid((unsigned)p.nb), block(RolloutShape<128, 8>::kThreads);
+    if (gen0) {
+      if (keep) go(k_rollout_few<true, true>, grid, block, p, g);
+      else go(k_rollout_few<true, false>, grid, block, p, g);
+    } else {
+      if (keep) go(k_rollout_few<false, true>, grid, block, p, g);
+      else go(k_rollout_few<false, false>, grid, block, p, g);
+    }
+  }
 }
 
 template <class Go>

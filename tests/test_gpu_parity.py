@@ -401,6 +401,35 @@ def test_mlp_bit_exact(name):
         assert deaths > 0
 
 
+@pytest.mark.parametrize("name,batch,T,keep,death", [
+    ("mlp64_cvt_b8192", 1, 1, True, 0),        # one individual, a spare wave beside it
+    ("mlp64_cvt_b8192", 5, 64, False, 0),      # odd batch; exactly one ring of steps
+    ("mlp64_cvt_b8192", 64, 65, True, 1),
+    ("mlp128_cvt_b65536", 1, 63, False, 0),    # eight waves per individual
+    ("mlp128_cvt_b65536", 256, 3, True, 2),    # its largest batch
+    ("mlp128_cvt_b65536", 40, 129, False, 1),
+    ("mlp128_cvt_b65536", 257, 66, False, 2),  # two waves per individual
+])
+def test_mlp_waves_per_individual(name, batch, T, keep, death):
+    """Each choice of waves per individual at the ends of its range and at
+    episode lengths around the reward ring's size, against the oracle."""
+    w = W.workload(name, batch=batch, T=T, C=200, death_mode=death, death_below=-0.06)
+    say(f"waves per individual: {name} N_B={batch} T={T} keep={keep} death={death}")
+    a = qd().Archive(w, keep_offspring=keep)
+    o = O.Oracle(w)
+    o.init()
+    for g in (0, 1, 2):
+        if g:
+            a.generation(g)
+            o.generation(g)
+        gb, ob = a.last_batch(), o.last_batch()
+        if keep:
+            np.testing.assert_array_equal(gb["geno"], o.last_offspring())
+        for k in ("fit", "desc", "cell", "won"):
+            np.testing.assert_array_equal(gb[k], ob[k], err_msg=f"{k} of generation {g}")
+    assert_archive_equal(a.snapshot(), o.archive(), o.n, "after two generations")
+
+
 @pytest.mark.parametrize("name,batch,samples", [("mlp64_cvt_b8192", 8192, 6),
                                                 ("mlp64_cvt_b8192", 131072, 4),
                                                 ("mlp128_cvt_b65536", 65536, 2)])
