@@ -233,6 +233,15 @@ __device__ __forceinline__ float sigmoid32(float x) {
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
 
+// Orders the LDS accesses of one wave's lanes around this point.  A wave's LDS
+// instructions execute in program order, so the compiler's order is all it
+// takes: no wait for a write before the reads that follow it.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Pairwise fold of one value per lane in the fixed tree h = 32, 16, ..., 1
 // (the partial of lane l is added to that of lane l + h), without LDS: the
 // steps h = 32 and 16 exchange halves and rows with the lane-swap

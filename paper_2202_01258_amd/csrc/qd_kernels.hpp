@@ -233,6 +233,30 @@ __device__ __forceinline__ void visit_bucket(const Params& p, int bucket, const 
   visit_range<D>(p, p.bucket_start[bucket], p.bucket_start[bucket + 1], u, best, best_idx);
 }
 
+// Whether the ring search may stop after ring r: a lower bound on the distance
+// to anything outside the visited box, or no bucket left.
+template <int D>
+__device__ __forceinline__ bool ring_done(const Params& p, const float* u, const int* qb, int r,
+                                          float best, int best_idx) {
+  const int R = p.bucket_res;
+  double bound = __builtin_inf();
+  bool face = false;
+#pragma unroll
+  for (int k = 0; k < D; ++k) {
+    if (qb[k] - r >= 1) {
+      const double gap = (double)u[k] - (double)(qb[k] - r) * p.inv_bucket_res - 1e-6;
+      bound = fmin(bound, gap > 0.0 ? gap * gap : 0.0);
+      face = true;
+    }
+    if (qb[k] + r + 1 <= R - 1) {
+      const double gap = (double)(qb[k] + r + 1) * p.inv_bucket_res - (double)u[k] - 1e-6;
+      bound = fmin(bound, gap > 0.0 ? gap * gap : 0.0);
+      face = true;
+    }
+  }
+  return !face || (best_idx != 0x7fffffff && (double)best * (1.0 + 1e-5) < bound);
+}
+
 template <int D>
 __device__ int cvt_cell(const Params& p, const float* d) {
   const int R = p.bucket_res;
@@ -321,24 +345,7 @@ __device__ int cvt_cell(const Params& p, const float* d) {
       }
     }
     }
-    // lower bound on the distance to anything outside the visited box
-    double bound = __builtin_inf();
-    bool face = false;
-#pragma unroll
-    for (int k = 0; k < D; ++k) {
-      if (qb[k] - r >= 1) {
-        const double gap = (double)u[k] - (double)(qb[k] - r) * p.inv_bucket_res - 1e-6;
-        bound = fmin(bound, gap > 0.0 ? gap * gap : 0.0);
-        face = true;
-      }
-      if (qb[k] + r + 1 <= R - 1) {
-        const double gap = (double)(qb[k] + r + 1) * p.inv_bucket_res - (double)u[k] - 1e-6;
-        bound = fmin(bound, gap > 0.0 ? gap * gap : 0.0);
-        face = true;
-      }
-    }
-    if (!face) break;
-    if (best_idx != 0x7fffffff && (double)best * (1.0 + 1e-5) < bound) break;
+    if (ring_done<D>(p, u, qb, r, best, best_idx)) break;
   }
   return best_idx;
 }
@@ -1071,13 +1078,30 @@ __device__ __forceinline__ int centroid_bucket(const Params& p, const float* c) 
   return b;
 }
 
+// Lloyd's algorithm in two dimensions finds nearest centroids through lists per
+// bucket of the ring-search grid.  The bucket structure's arrays, not built
+// yet, hold them: heads (0: empty, else centroid + 1) in one of two regions of
+// bucket_start, and centroid i with the list's next in bucket_pts[i].  The
+// regions take turns: an iteration reads one, clears the other, and the moved
+// centroids are linked into that.
+__device__ __forceinline__ int* lloyd_heads(const Params& p, int region) {
+  return p.bucket_start + region * (p.num_buckets + 1);
+}
+
+__device__ __forceinline__ void lloyd_link(const Params& p, int i, const float* c, int region) {
+  const int next = atomicExch(&lloyd_heads(p, region)[centroid_bucket(p, c)], i + 1);
+  p.bucket_pts[i] = make_float4(c[0], c[1], __int_as_float(next), 0.0f);
+}
+
 // Centroid i, coordinate k = 24-bit uniform of word k of block (i, 0, 0, CENTROID).
-__global__ void k_centroids(const Params p) {
+// link: the region of Lloyd's lists to put it in, or -1.
+__global__ void k_centroids(const Params p, int link) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= p.C) return;
   const uint4 x = philox((uint32_t)i, 0u, 0u, kTagCentroid, p.key);
   const float c[4] = {unit24(x.x), unit24(x.y), unit24(x.z), unit24(x.w)};
   for (int k = 0; k < p.D; ++k) p.cent[(size_t)i * p.D + k] = c[k];
+  if (link >= 0) lloyd_link(p, i, c, link);
 }
 
 // Centroids per bucket of the ring-search grid (counts at [1 .. num_buckets]).
@@ -1092,15 +1116,112 @@ __global__ void k_bucket_count(const Params p) {
 // Lloyd's algorithm for a centroidal Voronoi tessellation, one iteration in
 // two kernels.  Assignment: point i (coordinate k = U24 of word k of block
 // (i, 0, 0, CVT_SAMPLE)) goes to its nearest centroid by the cell rule (fma
-// chain over the dimensions, first minimum in index order); the centroids
-// pass through LDS in tiles of kLloydTile, in index order.  Each point adds
+// chain over the dimensions, first minimum in index order).  Each point adds
 // its coordinates' 24-bit numerators and a count to its centroid's
 // accumulators -- integer sums, so the order of the atomics does not matter.
+// Up to 2^kLloydSumBits / 2^24 points the count goes above coordinate 0's sum in
+// one word: the atomics are what an iteration in two dimensions takes its time
+// for (100000 points: 25 us with three per point, 20 us with two).
 constexpr int kLloydBlock = 256;
 constexpr int kLloydTile = 1024;
+constexpr int kLloydSumBits = 44;
+
+__device__ __forceinline__ bool lloyd_packed(const Params& p) {
+  return p.cvt_samples <= (1 << (kLloydSumBits - 24));
+}
 
 template <int D>
-__global__ __launch_bounds__(kLloydBlock) void k_lloyd_assign(const Params p) {
+__device__ __forceinline__ void lloyd_add(const Params& p, int c, const uint32_t* m) {
+  unsigned long long* a = p.lloyd_acc + (size_t)c * (D + 1);
+  const bool packed = lloyd_packed(p);
+#pragma unroll
+  for (int k = 0; k < D; ++k)
+    atomicAdd(a + k, (unsigned long long)m[k] + (k == 0 && packed ? 1ull << kLloydSumBits : 0ull));
+  if (!packed) atomicAdd(a + D, 1ull);
+}
+
+// Two dimensions: the exact ring search of cvt_cell, over the lists.  A ring's
+// lists are walked side by side, one round trip per node of the longest (about
+// every wave has a lane that needs ring 2).  A list holds about one centroid, so a point meets some nine of them
+// where all C were measured before: 100000 points on 10^4 centroids take
+// 20 us an iteration against 275 us, the bound now being the chain of
+// dependent loads and the atomics.
+__global__ __launch_bounds__(kLloydBlock) void k_lloyd_assign2(const Params p, int region) {
+  const int i = blockIdx.x * kLloydBlock + threadIdx.x;
+  const int* heads = lloyd_heads(p, region);
+  int* spare = lloyd_heads(p, region ^ 1);
+  for (int b = i; b <= p.num_buckets; b += (int)gridDim.x * kLloydBlock) spare[b] = 0;
+  if (i >= p.cvt_samples) return;
+  const uint4 x = philox((uint32_t)i, 0u, 0u, kTagCvtSample, p.key);
+  const uint32_t m[2] = {x.x >> 8, x.y >> 8};
+  const float u[2] = {(float)m[0] * 0x1p-24f, (float)m[1] * 0x1p-24f};
+  const int R = p.bucket_res;
+  int qb[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int b = (int)(u[k] * (float)R);
+    qb[k] = b > R - 1 ? R - 1 : b;
+  }
+  float best = __builtin_inff();
+  int best_idx = 0x7fffffff;
+  // walks N lists side by side: one round trip per node of the longest
+  const auto walk = [&](auto& at) {
+    constexpr int N = sizeof(at) / sizeof(at[0]);
+    for (;;) {
+      int any = 0;
+#pragma unroll
+      for (int k = 0; k < N; ++k) any |= at[k];
+      if (any == 0) break;
+      float4 c[N];
+#pragma unroll
+      for (int k = 0; k < N; ++k)
+        c[k] = at[k] != 0 ? p.bucket_pts[at[k] - 1] : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        if (at[k] != 0) {
+          const float e0 = u[0] - c[k].x;
+          float acc = fma32(e0, e0, 0.0f);
+          const float e1 = u[1] - c[k].y;
+          acc = fma32(e1, e1, acc);
+          const int idx = at[k] - 1;
+          if (acc < best || (acc == best && idx < best_idx)) {
+            best = acc;
+            best_idx = idx;
+          }
+          at[k] = __float_as_int(c[k].z);
+        }
+      }
+    }
+  };
+  const auto head = [&](int b0, int b1) {
+    return b0 >= 0 && b0 < R && b1 >= 0 && b1 < R ? heads[b0 * R + b1] : 0;
+  };
+  int at[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) at[k] = head(qb[0] + k / 3 - 1, qb[1] + k % 3 - 1);
+  walk(at);
+  // further rings, sixteen buckets at a time (8 r buckets on ring r: 2 r on each side)
+  for (int r = 1; !ring_done<2>(p, u, qb, r, best, best_idx);) {
+    ++r;
+    for (int k0 = 0; k0 < 8 * r; k0 += 16) {
+      int ring[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        const int e = k0 + k, side = e / (2 * r), o = e - side * 2 * r - r;
+        const int o0 = side == 0 ? -r : (side == 1 ? o : (side == 2 ? r : -o));
+        const int o1 = side == 0 ? o : (side == 1 ? r : (side == 2 ? -o : -r));
+        ring[k] = e < 8 * r ? head(qb[0] + o0, qb[1] + o1) : 0;
+      }
+      walk(ring);
+    }
+  }
+  lloyd_add<2>(p, best_idx, m);
+}
+
+// Four dimensions: every centroid, through LDS in tiles of kLloydTile, in index
+// order (a ring of the four-dimensional grid holds too many buckets).
+__global__ __launch_bounds__(kLloydBlock) void k_lloyd_assign4(const Params p) {
+  constexpr int D = 4;
   __shared__ float4 s_c[kLloydTile];
   const int i = blockIdx.x * kLloydBlock + threadIdx.x;
   const bool live = i < p.cvt_samples;
@@ -1114,77 +1235,81 @@ __global__ __launch_bounds__(kLloydBlock) void k_lloyd_assign(const Params p) {
   for (int t0 = 0; t0 < p.C; t0 += kLloydTile) {
     const int n = p.C - t0 < kLloydTile ? p.C - t0 : kLloydTile;
     __syncthreads();
-    for (int t = threadIdx.x; t < n; t += kLloydBlock) {
-      const float* c = p.cent + (size_t)(t0 + t) * D;
-      float4 v = make_float4(c[0], c[1], 0.0f, 0.0f);
-      if (D == 4) {
-        v.z = c[2];
-        v.w = c[3];
-      }
-      s_c[t] = v;
-    }
+    for (int t = threadIdx.x; t < n; t += kLloydBlock)
+      s_c[t] = reinterpret_cast<const float4*>(p.cent)[t0 + t];
     __syncthreads();
     for (int t = 0; t < n; ++t) {
-      const float4 c = s_c[t];
-      const float e0 = u[0] - c.x;
-      float acc = fma32(e0, e0, 0.0f);
-      const float e1 = u[1] - c.y;
-      acc = fma32(e1, e1, acc);
-      if (D == 4) {
-        const float e2 = u[D > 2 ? 2 : 0] - c.z;
-        acc = fma32(e2, e2, acc);
-        const float e3 = u[D > 3 ? 3 : 0] - c.w;
-        acc = fma32(e3, e3, acc);
-      }
+      const float acc = cvt_dist4(u, s_c[t]);
       if (acc < best) {
         best = acc;
         best_idx = t0 + t;
       }
     }
   }
-  if (live) {
-    unsigned long long* a = p.lloyd_acc + (size_t)best_idx * (D + 1);
-#pragma unroll
-    for (int k = 0; k < D; ++k) atomicAdd(a + k, (unsigned long long)m[k]);
-    atomicAdd(a + D, 1ull);
-  }
+  if (live) lloyd_add<D>(p, best_idx, m);
 }
 
 // Update: a centroid that received points moves to their mean,
 // ((double)sum / (double)count) 2^-24 rounded to fp32; the accumulators are
-// cleared for the next iteration.
-__global__ void k_lloyd_update(const Params p) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= p.C) return;
-  unsigned long long* a = p.lloyd_acc + (size_t)c * (p.D + 1);
-  const unsigned long long cnt = a[p.D];
-  if (cnt != 0ull) {
-    for (int k = 0; k < p.D; ++k)
-      p.cent[(size_t)c * p.D + k] = (float)(((double)a[k] / (double)cnt) * 0x1p-24);
+// cleared for the next iteration.  link 0 or 1: the region of the lists (just
+// cleared) that the centroids go into; kLloydLast: the last iteration, which
+// counts them per bucket instead (k_bucket_count's work; region 0 is clear) and
+// clears region 1, the cursors; -1: neither.
+constexpr int kLloydLast = 2;
+
+__global__ void k_lloyd_update(const Params p, int link) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= p.C) return;
+  unsigned long long* a = p.lloyd_acc + (size_t)i * (p.D + 1);
+  const bool packed = lloyd_packed(p);
+  const unsigned long long cnt = packed ? a[0] >> kLloydSumBits : a[p.D];
+  if (packed) a[0] &= (1ull << kLloydSumBits) - 1ull;
+  float c[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int k = 0; k < p.D; ++k) {
+    float* v = p.cent + (size_t)i * p.D + k;
+    c[k] = *v;
+    if (cnt != 0ull) *v = c[k] = (float)(((double)a[k] / (double)cnt) * 0x1p-24);
   }
   for (int k = 0; k <= p.D; ++k) a[k] = 0ull;
+  if (link == kLloydLast) {
+    if (i < p.num_buckets) lloyd_heads(p, 1)[i] = 0;
+    atomicAdd(&p.bucket_start[centroid_bucket(p, c) + 1], 1);
+  } else if (link >= 0) {
+    lloyd_link(p, i, c, link);
+  }
 }
 
+// Counts at [1 .. num_buckets] to starts (an inclusive scan), one workgroup,
+// kScanItems consecutive counts per thread: 10^4 buckets take two rounds of
+// barriers (10.6 us; one count per thread 12.3 us).
+constexpr int kScanItems = 8;
+
 __global__ __launch_bounds__(1024) void k_bucket_scan(const Params p) {
-  // inclusive scan of counts stored at [1..NB] -> starts; single workgroup
   __shared__ int carry;
   __shared__ int wsum[16];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (tid == 0) carry = 0;
   __syncthreads();
   const int NB = p.num_buckets;
-  for (int start = 1; start <= NB; start += 1024) {
-    const int i = start + tid;
-    int v = i <= NB ? p.bucket_start[i] : 0;
+  for (int start = 1; start <= NB; start += 1024 * kScanItems) {
+    const int i = start + tid * kScanItems;
+    int v[kScanItems];
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) v[k] = i + k <= NB ? p.bucket_start[i + k] : 0;
+#pragma unroll
+    for (int k = 1; k < kScanItems; ++k) v[k] += v[k - 1];
+    int sum = v[kScanItems - 1];
     for (int h = 1; h < 64; h <<= 1) {
-      const int o = __shfl_up(v, h, 64);
-      if (lane >= h) v += o;
+      const int o = __shfl_up(sum, h, 64);
+      if (lane >= h) sum += o;
     }
-    if (lane == 63) wsum[wave] = v;
+    if (lane == 63) wsum[wave] = sum;
     __syncthreads();
-    int off = carry;
+    int off = carry + sum - v[kScanItems - 1];
     for (int w = 0; w < wave; ++w) off += wsum[w];
-    if (i <= NB) p.bucket_start[i] = v + off;
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k)
+      if (i + k <= NB) p.bucket_start[i + k] = v[k] + off;
     __syncthreads();
     if (tid == 0) {
       int t = 0;
@@ -1214,68 +1339,92 @@ __global__ void k_bucket_fill(const Params p) {
 // so a centroid whose nearest-point distance to the box exceeds Dmax (with a
 // relative margin of 1e-5, far above the fp32 error of the distances the
 // search compares) is never the argmin for a point of the box.  The rest are
-// listed in ascending index; the count keeps counting past QD_CAND_SLOTS.
-// kCandGroup lanes per bucket walk the centroids together, staged in LDS
-// tiles: at step i lane q of the group takes centroid kCandGroup i + q.  The
-// bound is the group's minimum (order-free); the listed centroids are
-// appended in q order at each step, i.e. in ascending index.
-constexpr int kCandTile = 2048, kCandGroup = 16, kCandBuckets = 256 / kCandGroup;
+// counted, and listed in ascending index if they are at most QD_CAND_SLOTS.
+// kCandGroup lanes per fine bucket measure the centroids of a window of the
+// ring-search grid around the box: every row of the window is one run of
+// bucket_pts.  The window is wide enough once the distance from the box to
+// anything outside it exceeds the limit that its own centroids set, since then
+// no centroid outside changes the limit or is listed.  The hits are then put in
+// index order.  (Measured against walking all 10^4 centroids for each of 40000
+// buckets: 15 us against 506 us.)
+constexpr int kCandGroup = 16, kCandBuckets = 256 / kCandGroup;
 
 __global__ __launch_bounds__(256) void k_cand_build(const Params p) {
   constexpr int G = kCandGroup;
-  static_assert(G == 4 || G == 8 || G == 16, "a group is a power of two within a row");
-  __shared__ float2 s_c[kCandTile];
+  static_assert(G == 16, "a group is a row of lanes");
+  __shared__ int s_hit[kCandBuckets][QD_CAND_SLOTS];
   const int lane = lane_id(), q = lane & (G - 1);
   const int b = blockIdx.x * kCandBuckets + (int)(threadIdx.x / G);
-  const bool live = b < p.cand_buckets;
-  const int R = p.cand_res;
-  const double w = 1.0 / (double)R, pad = 1e-6;
-  const int bb = live ? b : 0;
-  const double lo0 = (bb / R) * w - pad, hi0 = (bb / R + 1) * w + pad;
-  const double lo1 = (bb % R) * w - pad, hi1 = (bb % R + 1) * w + pad;
-  const float2* cent = reinterpret_cast<const float2*>(p.cent);
-  double dmax = __builtin_inf();
-  for (int t0 = 0; t0 < p.C; t0 += kCandTile) {
-    const int tn = p.C - t0 < kCandTile ? p.C - t0 : kCandTile;
-    __syncthreads();
-    for (int e = threadIdx.x; e < tn; e += 256) s_c[e] = cent[t0 + e];
-    __syncthreads();
-    for (int e = q; e < tn; e += G) {
-      const double x = s_c[e].x, y = s_c[e].y;
-      const double fx = fmax(x - lo0, hi0 - x), fy = fmax(y - lo1, hi1 - y);
-      dmax = fmin(dmax, fx * fx + fy * fy);
-    }
-  }
+  if (b >= p.cand_buckets) return;
+  int* hits = s_hit[threadIdx.x / G];
+  const int Rf = p.cand_res, R = p.bucket_res;
+  const double w = 1.0 / (double)Rf, pad = 1e-6;
+  const double lo[2] = {(b / Rf) * w - pad, (b % Rf) * w - pad};
+  const double hi[2] = {(b / Rf + 1) * w + pad, (b % Rf + 1) * w + pad};
+  int c0[2], c1[2], w0[2], w1[2];
 #pragma unroll
-  for (int h = 1; h < G; h <<= 1) dmax = fmin(dmax, __shfl_xor(dmax, h, 64));   // group minimum
-  const double limit = dmax * (1.0 + 1e-5) + 1e-12;
+  for (int k = 0; k < 2; ++k) {
+    const int l = (int)floor(lo[k] * (double)R), h = (int)floor(hi[k] * (double)R);
+    c0[k] = l < 0 ? 0 : l;
+    c1[k] = h > R - 1 ? R - 1 : h;
+  }
+  double limit;
+  for (int r = 1;; ++r) {
+    double gap = __builtin_inf();
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      w0[k] = c0[k] - r < 0 ? 0 : c0[k] - r;
+      w1[k] = c1[k] + r > R - 1 ? R - 1 : c1[k] + r;
+      // 1e-6 covers the rounding of a centroid's bucket index
+      if (w0[k] > 0) gap = fmin(gap, lo[k] - (double)w0[k] * p.inv_bucket_res - 1e-6);
+      if (w1[k] < R - 1) gap = fmin(gap, (double)(w1[k] + 1) * p.inv_bucket_res - hi[k] - 1e-6);
+    }
+    double dmax = __builtin_inf();
+    for (int row = w0[0]; row <= w1[0]; ++row) {
+      const int s0 = p.bucket_start[row * R + w0[1]], s1 = p.bucket_start[row * R + w1[1] + 1];
+      for (int e = s0 + q; e < s1; e += G) {
+        const float4 c = p.bucket_pts[e];
+        const double x = c.x, y = c.y;
+        const double fx = fmax(x - lo[0], hi[0] - x), fy = fmax(y - lo[1], hi[1] - y);
+        dmax = fmin(dmax, fx * fx + fy * fy);
+      }
+    }
+#pragma unroll
+    for (int h = 1; h < G; h <<= 1) dmax = fmin(dmax, __shfl_xor(dmax, h, 64));   // group minimum
+    limit = dmax * (1.0 + 1e-5) + 1e-12;
+    if (gap == __builtin_inf() || (gap > 0.0 && gap * gap > limit)) break;
+  }
+  const auto within = [&](const float4& c) {
+    const double x = c.x, y = c.y;
+    const double gx = fmax(0.0, fmax(lo[0] - x, x - hi[0])), gy = fmax(0.0, fmax(lo[1] - y, y - hi[1]));
+    return gx * gx + gy * gy <= limit;
+  };
   int count = 0;
-  float4* out = p.cand_pts + (size_t)bb * QD_CAND_SLOTS;
+  float4* out = p.cand_pts + (size_t)b * QD_CAND_SLOTS;
+  const float2* cent = reinterpret_cast<const float2*>(p.cent);
   const int group0 = lane & ~(G - 1);
   const uint32_t gmask = (uint32_t)((1ull << G) - 1ull);
-  for (int t0 = 0; t0 < p.C; t0 += kCandTile) {
-    const int tn = p.C - t0 < kCandTile ? p.C - t0 : kCandTile;
-    __syncthreads();
-    for (int e = threadIdx.x; e < tn; e += 256) s_c[e] = cent[t0 + e];
-    __syncthreads();
-    for (int e0 = 0; e0 < tn; e0 += G) {   // the group's centroids e0 .. e0 + G - 1
+  for (int row = w0[0]; row <= w1[0]; ++row) {
+    const int s0 = p.bucket_start[row * R + w0[1]], s1 = p.bucket_start[row * R + w1[1] + 1];
+    for (int e0 = s0; e0 < s1; e0 += G) {
       const int e = e0 + q;
-      bool hit = false;
-      float2 c = make_float2(0.0f, 0.0f);
-      if (e < tn) {
-        c = s_c[e];
-        const double x = c.x, y = c.y;
-        const double gx = fmax(0.0, fmax(lo0 - x, x - hi0)), gy = fmax(0.0, fmax(lo1 - y, y - hi1));
-        hit = gx * gx + gy * gy <= limit;
-      }
+      const bool hit = e < s1 && within(p.bucket_pts[e]);
       const uint32_t bits = (uint32_t)(__ballot(hit) >> group0) & gmask;
       const int pos = count + __popc(bits & ((1u << q) - 1u));
-      if (live && hit && pos < QD_CAND_SLOTS)
-        out[pos] = make_float4(c.x, c.y, __int_as_float(t0 + e), 0.0f);
+      if (hit && pos < QD_CAND_SLOTS) hits[pos] = p.bucket_idx[e];
       count += __popc(bits);
     }
   }
-  if (live && q == 0) p.cand_count[b] = count;
+  wave_sync();
+  static_assert(QD_CAND_SLOTS <= G, "one hit per lane");
+  if (count <= QD_CAND_SLOTS && q < count) {   // (a longer list is never read)
+    const int idx = hits[q];
+    int rank = 0;
+    for (int t = 0; t < count; ++t) rank += hits[t] < idx ? 1 : 0;
+    const float2 c = cent[idx];
+    out[rank] = make_float4(c.x, c.y, __int_as_float(idx), 0.0f);
+  }
+  if (q == 0) p.cand_count[b] = count;
 }
 
 // Entry e of [A | B | s0] = 0.1 * normal (e mod 4) of block (e/4, 0, 0, ENV).
@@ -1295,7 +1444,7 @@ __global__ void k_env(const Params p, int count) {
 // The Gaussian sampler's table reaches the workspace as kernel arguments,
 // kTableChunk rows per launch, so that writing it needs no host buffer the
 // copy engine would have to read.
-constexpr int kTableChunk = 128;
+constexpr int kTableChunk = 193;   // half of the table: 3 KiB of arguments
 struct TableChunk {
   float4 rows[kTableChunk];
 };

@@ -518,18 +518,23 @@ qd_status qd_archive_init(const qd_config* cfg, void* d_workspace, uint64_t work
     const Go go{h, s, QD_K_SETUP};
     go(qd::k_clear_archive, dim3(1024), dim3(256), p, 1);
     if (p.tess == qd::kTessCvt) {
-      go(qd::k_centroids, dim3(blocks_for(p.C, 256)), dim3(256), p);
-      if (p.lloyd_acc) {
-        for (int it = 0; it < cfg->cvt_iters; ++it) {
-          const dim3 grid(blocks_for((uint64_t)p.cvt_samples, qd::kLloydBlock)), block(qd::kLloydBlock);
-          if (p.D == 2) go(qd::k_lloyd_assign<2>, grid, block, p);
-          else go(qd::k_lloyd_assign<4>, grid, block, p);
-          go(qd::k_lloyd_update, dim3(blocks_for(p.C, 256)), dim3(256), p);
-        }
+      // Lloyd's iterations in two dimensions go through lists per bucket, whose
+      // two regions take turns so that the last iteration reads region 1
+      const int iters = p.lloyd_acc ? cfg->cvt_iters : 0;
+      const bool lists = p.D == 2 && iters > 0;
+      const dim3 per_cell(blocks_for(p.C, 256)), block(256);
+      go(qd::k_centroids, per_cell, block, p, lists ? iters & 1 : -1);
+      for (int it = 0; it < iters; ++it) {
+        const dim3 grid(blocks_for((uint64_t)p.cvt_samples, qd::kLloydBlock)), lblock(qd::kLloydBlock);
+        const int region = (iters - it) & 1;
+        if (lists) go(qd::k_lloyd_assign2, grid, lblock, p, region);
+        else go(qd::k_lloyd_assign4, grid, lblock, p);
+        go(qd::k_lloyd_update, per_cell, block, p,
+           !lists ? -1 : (it + 1 == iters ? qd::kLloydLast : region ^ 1));
       }
-      go(qd::k_bucket_count, dim3(blocks_for(p.C, 256)), dim3(256), p);
+      if (!lists) go(qd::k_bucket_count, per_cell, block, p);
       go(qd::k_bucket_scan, dim3(1), dim3(1024), p);
-      go(qd::k_bucket_fill, dim3(blocks_for(p.C, 256)), dim3(256), p);
+      go(qd::k_bucket_fill, per_cell, block, p);
       if (p.cand_buckets > 0) go(qd::k_cand_build, dim3(blocks_for(p.cand_buckets, qd::kCandBuckets)), dim3(256), p);
     }
     if (p.task == qd::kTaskMlp) {

@@ -142,15 +142,6 @@ __device__ __forceinline__ float quad_dot(const float (&w)[R][M], const float4 (
   return quad_fold<R>(acc);
 }
 
-// Orders the LDS accesses of one wave's lanes around this point.  A wave's LDS
-// instructions execute in program order, so the compiler's order is all it
-// takes: no wait for a write before the reads that follow it.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Keeps a value in a register of its own (an empty asm that claims to change
 // it): the optimiser no longer derives other registers from how it was made.
 template <class T>

@@ -118,6 +118,50 @@ def test_lloyd_centroids_bit_exact(C, D, S, L):
     assert np.any(got != q.centroids()), "Lloyd iterations moved no centroid"
 
 
+@pytest.mark.parametrize("C,S,L", [
+    (1, 10, 1), (2, 1, 2), (3, 100, 3), (5, 4000, 2),      # grids of one and two buckets a side
+    (5, 1 << 20, 1), (5, (1 << 20) + 1, 2),                # count packed into a sum's word, and apart
+    (4100, 255, 4), (4100, 30001, 1),                      # most cells without points; many rings
+])
+def test_lloyd_lists_bit_exact(C, S, L):
+    """Lloyd's lists per bucket in two dimensions at the ends of their ranges:
+    centroids and first batch against the oracle (brute force)."""
+    w = W.workload("rastrigin_proj_cvt_b65536", n=16, C=C, batch=300, cvt_samples=S, cvt_iters=L,
+                   seed=3, init_lo=-5.12, init_hi=5.12)
+    say(f"lloyd lists C={C} S={S} L={L}")
+    a = qd().Archive(w)
+    o = O.Oracle(w)
+    o.init()
+    np.testing.assert_array_equal(a.views()["centroids"].cpu().numpy(), o.centroids())
+    np.testing.assert_array_equal(a.last_batch()["cell"], o.last_batch()["cell"])
+
+
+@pytest.mark.parametrize("C,L", [(1, 0), (2, 0), (3, 2), (37, 0), (500, 3), (3003, 0)])
+def test_cvt_candidate_lists_complete(C, L):
+    """A fine bucket's count and list are those of the definition worked out
+    over every centroid in double: nearest-point distance to the padded box at
+    most the smallest farthest-corner distance, in ascending index."""
+    w = W.workload("rastrigin_proj_cvt_b65536", n=16, C=C, batch=16, seed=5,
+                   cvt_samples=2000 if L else 0, cvt_iters=L)
+    say(f"candidate lists against the definition, C={C} L={L}")
+    a = qd().Archive(w)
+    v = a.views()
+    R = a.layout.cand_res
+    cnt, pts = v["cand_count"].cpu().numpy(), v["cand_pts"].cpu().numpy()
+    cent = v["centroids"].cpu().numpy().astype(np.float64)
+    for b in range(R * R):
+        # the box as the kernel forms it: w = 1 / R, padded by 1e-6
+        box = [((i * (1.0 / R)) - 1e-6, (i + 1) * (1.0 / R) + 1e-6) for i in (b // R, b % R)]
+        far = sum(np.maximum(cent[:, k] - lo, hi - cent[:, k]) ** 2 for k, (lo, hi) in enumerate(box))
+        near = sum(np.maximum(0.0, np.maximum(lo - cent[:, k], cent[:, k] - hi)) ** 2
+                   for k, (lo, hi) in enumerate(box))
+        want = np.nonzero(near <= far.min() * (1.0 + 1e-5) + 1e-12)[0]
+        assert cnt[b] == len(want), (b, cnt[b], len(want))
+        if len(want) <= qd().CAND_SLOTS:
+            np.testing.assert_array_equal(pts[b, : len(want), 2].view(np.int32), want)
+            np.testing.assert_array_equal(pts[b, : len(want), :2], cent[want].astype(np.float32))
+
+
 @pytest.mark.parametrize("C,seed", [(10000, 0), (2000, 3), (37, 1)])
 def test_cvt_candidate_lists_hold_the_nearest_centroid(C, seed):
     """Every listed fine bucket holds, in ascending order, the brute-force
