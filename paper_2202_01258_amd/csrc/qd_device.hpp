@@ -51,6 +51,56 @@ __device__ __forceinline__ uint4 philox(uint32_t c0, uint32_t c1, uint32_t c2, u
   return make_uint4(c0, c1, c2, c3);
 }
 
+// philox() for many individuals at the same items: what does not depend on the
+// individual (counter word 1) -- one product in each of the first three rounds
+// -- is worked out once per item, the rest is finished per individual.
+struct PhiloxItem {
+  uint32_t a, b, h, l;
+};
+struct PhiloxIndividual {
+  uint32_t hi, lo;                                     // of round 2's first product
+};
+
+__device__ __forceinline__ PhiloxItem philox_item(uint32_t c0, uint32_t c2, uint32_t c3, Key key) {
+  const uint64_t m0 = (uint64_t)0xD2511F53u * c0;
+  const uint64_t m1 = (uint64_t)0xCD9E8D57u * c2;
+  const uint64_t m1b = (uint64_t)0xCD9E8D57u * xor3((uint32_t)(m0 >> 32), c3, key.k1);
+  const uint64_t m0c = (uint64_t)0xD2511F53u *
+                       xor3((uint32_t)(m1b >> 32), (uint32_t)m1, key.k0 + 0x9E3779B9u);
+  PhiloxItem v;
+  v.a = (uint32_t)m0 ^ (key.k1 + 0xBB67AE85u);
+  v.b = (uint32_t)m1b ^ (key.k0 + 2u * 0x9E3779B9u);
+  v.h = (uint32_t)(m0c >> 32) ^ (key.k1 + 2u * 0xBB67AE85u);
+  v.l = (uint32_t)m0c;
+  return v;
+}
+
+__device__ __forceinline__ PhiloxIndividual philox_individual(uint32_t c1, uint32_t c2, Key key) {
+  const uint64_t m1 = (uint64_t)0xCD9E8D57u * c2;
+  const uint64_t m0 = (uint64_t)0xD2511F53u * ((uint32_t)(m1 >> 32) ^ c1 ^ key.k0);
+  return PhiloxIndividual{(uint32_t)(m0 >> 32), (uint32_t)m0};
+}
+
+__device__ __forceinline__ uint4 philox_finish(const PhiloxItem& v, const PhiloxIndividual& w, Key key) {
+  const uint64_t m1c = (uint64_t)0xCD9E8D57u * (v.a ^ w.hi);
+  uint32_t c0 = (uint32_t)(m1c >> 32) ^ v.b, c1 = (uint32_t)m1c, c2 = v.h ^ w.lo, c3 = v.l;
+  uint32_t k0 = key.k0 + 3u * 0x9E3779B9u, k1 = key.k1 + 3u * 0xBB67AE85u;
+#pragma unroll
+  for (int round = 3; round < 10; ++round) {
+    const uint64_t m0 = (uint64_t)0xD2511F53u * c0;
+    const uint64_t m1 = (uint64_t)0xCD9E8D57u * c2;
+    const uint32_t n0 = xor3((uint32_t)(m1 >> 32), c1, k0);
+    const uint32_t n2 = xor3((uint32_t)(m0 >> 32), c3, k1);
+    c0 = n0;
+    c1 = (uint32_t)m1;
+    c2 = n2;
+    c3 = (uint32_t)m0;
+    k0 += 0x9E3779B9u;
+    k1 += 0xBB67AE85u;
+  }
+  return make_uint4(c0, c1, c2, c3);
+}
+
 __device__ __forceinline__ float unit24(uint32_t x) {        // [0, 1)
   return (float)(x >> 8) * 0x1p-24f;
 }
@@ -276,6 +326,48 @@ __device__ __forceinline__ void row_bcast8(float v, float (&out)[8]) {
           : "v"(v));
 }
 
+// Keeps a value in a register of its own (an empty asm that claims to change
+// it): the optimiser no longer derives other registers from how it was made.
+template <class T>
+__device__ __forceinline__ void hold(T& v) { __asm__ volatile("" : "+v"(v)); }
+
+// Makes a scalar opaque to the optimiser (an empty asm that claims to change
+// it), so that what follows from it is worked out where it is used.
+__device__ __forceinline__ void hold_scalar(int& v) { __asm__ volatile("" : "+s"(v)); }
+
+// A lane's value, in a scalar register.
+template <class T>
+__device__ __forceinline__ T from_lane(T v, int lane) {
+  return __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+}
+
+// Lane 0 of each row of 16 lanes, in all its lanes.
+__device__ __forceinline__ float row_first(float v) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0x150, 0xf, 0xf, true));
+}
+
+// From a value per part (64 / OPW lanes) to one per half: of four parts out[0]
+// gets parts 0 and 2 in its halves, out[1] parts 1 and 3.
+template <int OPW, class T>
+__device__ __forceinline__ void halves_of_parts(T v, T (&out)[(OPW + 1) / 2]) {
+  if constexpr (OPW != 4) {
+    out[0] = v;
+  } else {
+    const uint32_t b = __builtin_bit_cast(uint32_t, v);
+    const auto s = __builtin_amdgcn_permlane16_swap(b, b, false, false);
+    const uint32_t even = s[0], odd = s[1];   // (a bit_cast of an element takes the vector's first)
+    out[0] = __builtin_bit_cast(T, even);
+    out[1] = __builtin_bit_cast(T, odd);
+  }
+}
+
+// Rows 0 .. 3: the first rows of a's and b's halves, a's lower, b's lower, a's
+// upper, b's upper.
+__device__ __forceinline__ float rows_from_halves(float a, float b) {
+  const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(s[0]);
+}
+
 // One rotation step of a row-wide minimum of (value, index) pairs, smaller
 // index first among equal values.
 template <int N>
@@ -286,65 +378,59 @@ __device__ __forceinline__ void min_pair_row(float& v, int& idx) {
   v = take ? ov : v;
   idx = take ? oi : idx;
 }
-__device__ __forceinline__ float wave_fold_sum(float v) {
-  const auto h32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = __uint_as_float(h32[0]) + __uint_as_float(h32[1]);
-  const auto h16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = __uint_as_float(h16[0]) + __uint_as_float(h16[1]);
+
+// Folds of OPW offspring's partials at once, offspring i's total in every lane
+// of the i-th 64 / OPW lanes.  The first steps pack values into halves and rows
+// of one register (a half-swap of a with b leaves lane l of the sum holding
+// a_l + a_{l+32} below lane 32 and b's pair sums above; the row swap then does
+// the same for rows of 16 lanes), after which the rotations finish all of them.
+// Each value goes through exactly the pairs of wave_fold_sum.
+__device__ __forceinline__ float swap32_add(float a, float b) {
+  const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+__device__ __forceinline__ float swap16_add(float a, float b) {
+  const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+__device__ __forceinline__ float row_fold_sum(float v) {
   v = v + row_ror<8>(v);
   v = v + row_ror<4>(v);
   v = v + row_ror<2>(v);
-  v = v + row_ror<1>(v);
-  return v;
+  return v + row_ror<1>(v);
+}
+__device__ __forceinline__ float wave_fold_sum(float v) {
+  v = swap32_add(v, v);
+  return row_fold_sum(swap16_add(v, v));
+}
+template <int OPW>
+__device__ __forceinline__ float fold_offspring(const float (&v)[OPW]) {
+  if constexpr (OPW == 4) {
+    return row_fold_sum(swap16_add(swap32_add(v[0], v[2]), swap32_add(v[1], v[3])));
+  } else if constexpr (OPW == 2) {
+    const float h = swap32_add(v[0], v[1]);
+    return row_fold_sum(swap16_add(h, h));
+  } else {
+    return wave_fold_sum(v[0]);
+  }
 }
 
-// wave_fold_sum for partials that are zero in lanes 32 .. 63 of the wave the
-// R64 order describes (at most 128 genes: its h = 32 step adds +0 and changes
-// nothing), with two such waves packed into the two halves of this one: the
-// h = 16 .. 1 steps stay inside each half, whose every lane ends up with its
-// half's sum.
-__device__ __forceinline__ float half_fold_sum(float v) {
-  const auto h16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = __uint_as_float(h16[0]) + __uint_as_float(h16[1]);
-  v = v + row_ror<8>(v);
-  v = v + row_ror<4>(v);
-  v = v + row_ror<2>(v);
-  v = v + row_ror<1>(v);
-  return v;
+// The same for partials that are zero in lanes 32 .. 63 of the wave the R64
+// order describes (at most 128 genes: its h = 32 step adds +0 and changes
+// nothing), with two offspring's lanes packed into one register's halves: v[0]
+// holds offspring 0 and OPW / 2, v[1] offspring 1 and 3.
+template <int OPW>
+__device__ __forceinline__ float fold_halves(const float (&v)[(OPW + 1) / 2]) {
+  if constexpr (OPW == 4) return row_fold_sum(swap16_add(v[0], v[1]));
+  else return row_fold_sum(swap16_add(v[0], v[0]));
 }
 
 // Fold of 8 slices, lane l holding slice l / 8 of sum l mod 8: pairs of slices
 // four, two and one apart, the total in every lane.
 __device__ __forceinline__ float slice_fold_sum(float v) {
-  const auto h32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = __uint_as_float(h32[0]) + __uint_as_float(h32[1]);
-  const auto h16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = __uint_as_float(h16[0]) + __uint_as_float(h16[1]);
+  v = swap32_add(v, v);
+  v = swap16_add(v, v);
   return v + row_ror<8>(v);
-}
-
-// The same fold for three values at once.  The first two steps pack values
-// into halves and rows of one register (a half-swap of a with b leaves lane l
-// of the sum holding a_l + a_{l+32} below lane 32 and b's pair sums above;
-// the row swap then does the same for rows of 16 lanes), after which the
-// rotations finish all three in one register: a ends in lanes 0-15, c in
-// 16-31, b in 32-47.  Each value goes through exactly the pairs of
-// wave_fold_sum.
-__device__ __forceinline__ void wave_fold_sum3(float a, float b, float c, float& sa, float& sb,
-                                               float& sc) {
-  const auto ab = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-  const float pab = __uint_as_float(ab[0]) + __uint_as_float(ab[1]);
-  const auto cz = __builtin_amdgcn_permlane32_swap(__float_as_uint(c), 0u, false, false);
-  const float pcz = __uint_as_float(cz[0]) + __uint_as_float(cz[1]);
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(pab), __float_as_uint(pcz), false, false);
-  float v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-  v = v + row_ror<8>(v);
-  v = v + row_ror<4>(v);
-  v = v + row_ror<2>(v);
-  v = v + row_ror<1>(v);
-  sa = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), 0));
-  sc = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), 16));
-  sb = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), 32));
 }
 
 // Order-preserving map of an fp32 objective to u32 (-0 folded onto +0).

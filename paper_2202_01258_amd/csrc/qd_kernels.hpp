@@ -27,6 +27,8 @@
 //                 next selection draws from.
 #pragma once
 
+#include <type_traits>
+
 #include "../../include/qd.h"
 #include "qd_device.hpp"
 
@@ -130,6 +132,17 @@ __device__ __forceinline__ Pair recorded_pair(const Params& p, uint32_t g, int j
   return pair_from_record(p, g, j, p.off_par[2 * j], p.off_par[2 * j + 1], p.off_bank[j], tb);
 }
 
+// Algorithm 2 on four genes: theta1 + sigma1 eps1 + lambda (theta2 - theta1).
+__device__ __forceinline__ float4 vary4(const float4& t1, const float4& t2, const uint4& x, float s1,
+                                        float l, const Tables& tb) {
+  const float e0 = normal(x.x, tb), e1 = normal(x.y, tb);
+  const float e2 = normal(x.z, tb), e3 = normal(x.w, tb);
+  return make_float4(fma32(l, t2.x - t1.x, fma32(s1, e0, t1.x)),
+                     fma32(l, t2.y - t1.y, fma32(s1, e1, t1.y)),
+                     fma32(l, t2.z - t1.z, fma32(s1, e2, t1.z)),
+                     fma32(l, t2.w - t1.w, fma32(s1, e3, t1.w)));
+}
+
 // Genes base..base+3 of offspring j (base a multiple of 4).  GEN0: the random
 // first batch of a test function, lo + U (hi - lo).  Otherwise Algorithm 2:
 // theta1 + sigma1 eps1 + lambda (theta2 - theta1), eps1 from block base/4.
@@ -161,14 +174,8 @@ __device__ __forceinline__ float4 make_genes(const Params& p, const Pair& q, uin
     const uint32_t off = 4u * (uint32_t)base;
     const float4 t1 = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(q.row1) + off);
     const float4 t2 = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(q.row2) + off);
-    const uint4 x = philox((uint32_t)(base >> 2), (uint32_t)j, g, kTagIso, p.key);
-    const float e0 = normal(x.x, q.tb), e1 = normal(x.y, q.tb);
-    const float e2 = normal(x.z, q.tb), e3 = normal(x.w, q.tb);
-    const float s1 = p.iso_sigma, l = q.lambda;
-    return make_float4(fma32(l, t2.x - t1.x, fma32(s1, e0, t1.x)),
-                       fma32(l, t2.y - t1.y, fma32(s1, e1, t1.y)),
-                       fma32(l, t2.z - t1.z, fma32(s1, e2, t1.z)),
-                       fma32(l, t2.w - t1.w, fma32(s1, e3, t1.w)));
+    return vary4(t1, t2, philox((uint32_t)(base >> 2), (uint32_t)j, g, kTagIso, p.key), p.iso_sigma,
+                 q.lambda, q.tb);
   }
 }
 
@@ -350,17 +357,16 @@ __device__ int cvt_cell(const Params& p, const float* d) {
   return best_idx;
 }
 
-// Nearest centroid for four offspring at once, on a two-dimensional CVT with
-// candidate lists: the 16 lanes of row i take the descriptor (d0, d1) held by
-// lane i, look up its fine bucket and test one candidate each, then keep the
-// smallest (distance, index) pair of the row -- the brute-force argmin with
-// ties to the lower index, as the list holds every centroid that can win.
-// Lane i gets offspring i's cell: -1 for a NaN descriptor, -2 when its bucket
-// lists more than QD_CAND_SLOTS centroids or the descriptor lies outside the
-// box (the caller then runs the ring search).  Every lane must call it.
-__device__ __forceinline__ int cvt_cell_rows(const Params& p, float d0, float d1, int lane) {
-  const int row = lane >> 4, sub = lane & 15;
-  const float g0 = __shfl(d0, row, 64), g1 = __shfl(d1, row, 64);
+// Nearest centroid per row of 16 lanes, on a two-dimensional CVT with candidate
+// lists: the lanes of a row hold the same descriptor (g0, g1), look up its fine
+// bucket and test one candidate each, then keep the smallest (distance, index)
+// pair of the row -- the brute-force argmin with ties to the lower index, as the
+// list holds every centroid that can win.  The row's lanes get the cell: -1 for
+// a NaN descriptor, -2 when its bucket lists more than QD_CAND_SLOTS centroids
+// or the descriptor lies outside the box (the caller then runs the ring
+// search).  Every lane must call it.
+__device__ __forceinline__ int cvt_cell_rows(const Params& p, float g0, float g1, int lane) {
+  const int sub = lane & 15;
   const bool nan = !(g0 == g0 && g1 == g1);
   const float u0 = (g0 - p.lo[0]) / p.span[0];
   const float u1 = (g1 - p.lo[1]) / p.span[1];
@@ -390,9 +396,7 @@ __device__ __forceinline__ int cvt_cell_rows(const Params& p, float d0, float d1
   min_pair_row<1>(best, best_idx);
   // an empty list (never built: every bucket lists the centroid that sets its
   // distance bound) would leave best_idx unset; the ring search takes it then
-  const int res = nan ? -1
-                      : (inside && cnt <= QD_CAND_SLOTS && best_idx != 0x7fffffff ? best_idx : -2);
-  return __shfl(res, (lane & 3) * 16, 64);
+  return nan ? -1 : (inside && cnt <= QD_CAND_SLOTS && best_idx != 0x7fffffff ? best_idx : -2);
 }
 
 // Insertion key: order-preserving bits of the objective (-0 as +0), then
@@ -438,17 +442,27 @@ __device__ __forceinline__ void insert_one(const Params& p, int cell, uint64_t k
 
 // ---------------------------------------------------------------------------
 // Select + vary + evaluate + cell + insert (test functions).  A wave takes
-// OPW consecutive offspring: lanes 0 .. OPW-1 draw their parents together,
-// then the whole wave runs each offspring's genes in turn (lane l owns genes
-// 256c + 4l .. 256c + 4l + 3 of every chunk c, i.e. gene groups q = g/4 with
-// q mod 64 = l; its partial sums run in ascending gene order and the wave
-// folds them pairwise, h = 32 .. 1); finally lanes 0 .. OPW-1 find their
-// offspring's cell and insert its key.  Large batches take four offspring per
+// OPW consecutive offspring; the i-th 64 / OPW lanes draw offspring i's parents
+// and, at the end, find its cell and insert its key (their first lane speaks
+// for it).  In between the whole wave runs the genes chunk by chunk, each chunk
+// for every offspring in turn: lane l owns genes 256c + 4l .. 256c + 4l + 3 of
+// every chunk c, i.e. gene groups q = g/4 with q mod 64 = l; its partial sums
+// run in ascending gene order and the wave folds them pairwise, h = 32 .. 1, all
+// its offspring's in one register.  What a chunk's lanes need for any offspring
+// -- offsets, bounds, and one product of each of the generator's first three
+// rounds -- is worked out once per chunk.  Large batches take four offspring per
 // wave (the per-wave set-up -- sampler table, selection -- spread over more
 // work); small ones fewer, since there a generation is a chain of dependent
 // memory round trips and more waves in flight shorten it: one offspring per
 // wave up to kOneOffspringBatch, two up to kTwoOffspringBatch.  Every choice
 // gives the same bits (each offspring's arithmetic does not depend on it).
+//
+// Instruction issue bounds it while the parents' rows come from L2, ~140 VALU
+// instructions per offspring and chunk (with the offspring outermost, each
+// looking through the chunk's lanes for itself, 187), beside a fixed ~20 us per
+// 65536 offspring; parents spread over 10^4 rows add the fabric's time.  One
+// generation of 65536 offspring: n = 1000, one filled cell 61.3 -> 57.4 us; all
+// cells filled 86.1 -> 81.6 us; n = 100 20.8 -> 18.1 us.
 // ---------------------------------------------------------------------------
 constexpr int kOffspringPerWave = 4;             // the most a wave takes
 constexpr int kOneOffspringBatch = 2048;
@@ -458,206 +472,277 @@ inline int offspring_per_wave(int nb) {
   return nb <= kOneOffspringBatch ? 1 : (nb <= kTwoOffspringBatch ? 2 : kOffspringPerWave);
 }
 
+template <int I>
+using index = std::integral_constant<int, I>;
+
 template <int TASK, bool GEN0, bool KEEP, int OPW>
-__global__ __launch_bounds__(256) void k_vary_eval(const Params p, uint32_t g) {
+__global__ __launch_bounds__(256, OPW < 4 ? 1 : (TASK == kTaskProj ? 7 : 8))
+void k_vary_eval(const Params p, uint32_t g) {
+  // (seven waves per SIMD for projections: 70 registers; held at eight, spills
+  // cost more than the wave brings, 59.5 us against 57.0 us at n = 1000)
   static_assert(OPW == 1 || OPW == 2 || OPW == kOffspringPerWave, "one, two or four offspring");
+  constexpr int LPO = 64 / OPW;            // lanes that speak for an offspring
   __shared__ float4 s_ntab[kNormalRows];
   const Tables tb{s_ntab};
-  const int lane = threadIdx.x & 63;
-  const int j0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * OPW;
+  const int lane = threadIdx.x & 63, part = lane / LPO;
+  const int j0 = (int)(blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * OPW;
   const int nmine = p.nb - j0 < OPW ? p.nb - j0 : OPW;
-  const bool mine = lane < nmine;          // lane i speaks for offspring j0 + i
+  const bool speaks = lane % LPO == 0 && part < nmine;
+  // (parts without an offspring repeat the wave's last one)
+  const int my_j = j0 + (part < nmine ? part : nmine - 1);
 
   // The parents' cells and banks (Appendix A.2) are read while the sampler
   // table is being staged: the chain filled-cell count -> list entry -> bank
   // runs beside the table's loads; the line coefficient, which needs the
   // table, comes after the barrier.
-  Pair sel{nullptr, nullptr, 0.0f, -1, -1, 0u};
+  int par1 = -1, par2 = -1;                // cells, their banks in bit kBankBit (C is at most 2^28)
+  constexpr int kBankBit = 30;
+  float sel_lambda = 0.0f;
   int nocc = 0;
   uint32_t sel_z = 0u;
   if (!GEN0) {
     nocc = p.counters[0];
-    if (mine && nocc > 0) {
-      const uint4 x = philox(0u, (uint32_t)(j0 + lane), g, kTagSelect, p.key);
-      sel.c1 = pick(p.occ_list, x.x, nocc);
-      sel.c2 = pick(p.occ_list, x.y, nocc);
-      sel.banks = p.arch_slot[sel.c1] | (p.arch_slot[sel.c2] << 1);
+    if (nmine > 0 && nocc > 0) {
+      const uint4 x = philox(0u, (uint32_t)my_j, g, kTagSelect, p.key);
+      par1 = pick(p.occ_list, x.x, nocc);
+      par2 = pick(p.occ_list, x.y, nocc);
+      const uint32_t b1 = p.arch_slot[par1], b2 = p.arch_slot[par2];
+      par1 |= (int)(b1 << kBankBit);
+      par2 |= (int)(b2 << kBankBit);
       sel_z = x.z;
     }
     stage_normal_table(s_ntab, p.ntab, (int)threadIdx.x, 256);
     __syncthreads();
   }
-  if (j0 >= p.nb) return;
+  if (nmine <= 0) return;
   if (!GEN0) {
     if (nocc <= 0) {
-      if (mine) record_empty_archive(p, j0 + lane);
+      if (speaks) record_empty_archive(p, my_j);
       return;
     }
-    if (mine) {
-      sel.lambda = p.line_sigma * normal(sel_z, tb);
-      sel.row1 = geno_row(p, sel.banks & 1u, sel.c1);
-      sel.row2 = geno_row(p, (sel.banks >> 1) & 1u, sel.c2);
-    }
+    sel_lambda = p.line_sigma * normal(sel_z, tb);
   }
+  // a parent's row, counted over both banks (below 2^29)
+  const auto row_of = [&](int par) {
+    return (par >> kBankBit) * p.C + (par & ((1 << kBankBit) - 1));
+  };
+  const auto row = [&](int r) { return p.arch_geno + (size_t)r * (size_t)p.stride; };
 
   const int n = p.n;
   const int half = n >> 1;
-  float my_f = 0.0f, my_d0 = 0.0f, my_d1 = 0.0f;
-  if (TASK != kTaskProj && n <= 128) {
+  float f, d0 = 0.0f, d1 = 0.0f;           // the part's offspring: term sum, descriptor
+  if ((TASK != kTaskProj || OPW == 4) && n <= 128) {
+    // (projections only in large batches: n = 100, N_B = 65536 31.6 -> 21.0 us, while
+    // in small ones the code in between costs the longer genotypes 2%)
     // Short genotypes: two offspring at a time, one per 32-lane half (lane h
     // of a half owns genes 4h .. 4h + 3, as lane h of a whole wave would, and
-    // the fold stays in the half).  With an odd count the spare half repeats
-    // its partner and its result is dropped.
-    const int hl = lane >> 5, hlane = lane & 31;
-    for (int i = 0; i < nmine; i += 2) {
-      const int ib = i + 1 < nmine ? i + 1 : i;   // the upper half's offspring slot
-      const int j = j0 + (hl ? ib : i);
-      Pair q{nullptr, nullptr, 0.0f, -1, -1, 0u, tb};
-      if (!GEN0) {
-        const int c1a = __builtin_amdgcn_readlane(sel.c1, i), c1b = __builtin_amdgcn_readlane(sel.c1, ib);
-        const int c2a = __builtin_amdgcn_readlane(sel.c2, i), c2b = __builtin_amdgcn_readlane(sel.c2, ib);
-        const int bka = __builtin_amdgcn_readlane((int)sel.banks, i);
-        const int bkb = __builtin_amdgcn_readlane((int)sel.banks, ib);
-        const uint32_t lma = __builtin_amdgcn_readlane(__float_as_uint(sel.lambda), i);
-        const uint32_t lmb = __builtin_amdgcn_readlane(__float_as_uint(sel.lambda), ib);
-        q.c1 = hl ? c1b : c1a;
-        q.c2 = hl ? c2b : c2a;
-        q.banks = (uint32_t)(hl ? bkb : bka);
-        q.lambda = __uint_as_float(hl ? lmb : lma);
-        q.row1 = geno_row(p, q.banks & 1u, q.c1);
-        q.row2 = geno_row(p, (q.banks >> 1) & 1u, q.c2);
-      }
-      const int base = 4 * hlane;
-      float acc = 0.0f, g0 = 0.0f, g1 = 0.0f;
+    // the fold stays in the half); i and i + 2 of four, so that the folds leave
+    // offspring i in part i.
+    constexpr int kPasses = (OPW + 1) / 2;
+    const int base = 4 * (lane & 31);
+    // g0, g1: genes 0 and 1, or with a projection the clipped sums of the halves
+    float acc[kPasses], g0[kPasses], g1[kPasses];
+    float lambda[kPasses];
+    int row1[kPasses], row2[kPasses], jp[kPasses];
+    halves_of_parts<OPW>(row_of(par1), row1);
+    halves_of_parts<OPW>(row_of(par2), row2);
+    halves_of_parts<OPW>(sel_lambda, lambda);
+    halves_of_parts<OPW>(my_j, jp);
+    PhiloxItem item{};
+    if (!GEN0) item = philox_item((uint32_t)(base >> 2), g, kTagIso, p.key);
+#pragma unroll
+    for (int i = 0; i < kPasses; ++i) {
+      acc[i] = g0[i] = g1[i] = 0.0f;
       if (base < n) {
-        const float4 v4 = make_genes<GEN0>(p, q, g, j, base);
-        if (KEEP && (hl == 0 || ib != i))
-          *reinterpret_cast<float4*>(p.off_geno + (size_t)j * (size_t)p.stride + base) = v4;
-        g0 = v4.x;
-        g1 = v4.y;
-        const float v[4] = {v4.x, v4.y, v4.z, v4.w};
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-          if (base + k < n) acc = acc + task_term<TASK>(v[k]);
-      }
-      const float f = half_fold_sum(acc);
-      const float fa = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(f), 0));
-      const float fb = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(f), 32));
-      const float g0a = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(g0), 0));
-      const float g1a = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(g1), 0));
-      const float g0b = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(g0), 32));
-      const float g1b = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(g1), 32));
-      if (lane == i) {
-        my_f = -fa;
-        my_d0 = clip(g0a, p.lo[0], p.hi[0]);
-        my_d1 = clip(g1a, p.lo[1], p.hi[1]);
-      } else if (lane == ib) {
-        my_f = -fb;
-        my_d0 = clip(g0b, p.lo[0], p.hi[0]);
-        my_d1 = clip(g1b, p.lo[1], p.hi[1]);
-      }
-    }
-  } else
-  for (int i = 0; i < nmine; ++i) {
-    const int j = j0 + i;
-    Pair q{nullptr, nullptr, 0.0f, -1, -1, 0u, tb};
-    if (!GEN0) {
-      // lane i's selection, read into scalar registers (i is wave-uniform)
-      q.c1 = __builtin_amdgcn_readlane(sel.c1, i);
-      q.c2 = __builtin_amdgcn_readlane(sel.c2, i);
-      q.banks = (uint32_t)__builtin_amdgcn_readlane((int)sel.banks, i);
-      q.lambda = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(sel.lambda), i));
-      q.row1 = geno_row(p, q.banks & 1u, q.c1);
-      q.row2 = geno_row(p, (q.banks >> 1) & 1u, q.c2);
-    }
-    float acc = 0.0f, dlo = 0.0f, dhi = 0.0f;
-    float g0 = 0.0f, g1 = 0.0f;
-    float* keep_row = KEEP ? p.off_geno + (size_t)j * (size_t)p.stride : nullptr;
-    const int nchunks = (n + 255) >> 8;
-    for (int c = 0; c < nchunks; ++c) {   // a wave-uniform trip count
-      const int base = 256 * c + 4 * lane;
-      if (base >= n) continue;
-      const float4 v4 = make_genes<GEN0>(p, q, g, j, base);
-      if (KEEP) *reinterpret_cast<float4*>(keep_row + base) = v4;
-      if (base == 0) {
-        g0 = v4.x;
-        g1 = v4.y;
-      }
-      if (base + 4 <= n) {
-        // whole block: the same additions in the same order, without per-gene tests
-        acc = acc + task_term<TASK>(v4.x);
-        acc = acc + task_term<TASK>(v4.y);
-        acc = acc + task_term<TASK>(v4.z);
-        acc = acc + task_term<TASK>(v4.w);
-        if (TASK == kTaskProj) {
-          if (base + 4 <= half) {
-            dlo = dlo + clip(v4.x, p.lo[0], p.hi[0]);
-            dlo = dlo + clip(v4.y, p.lo[0], p.hi[0]);
-            dlo = dlo + clip(v4.z, p.lo[0], p.hi[0]);
-            dlo = dlo + clip(v4.w, p.lo[0], p.hi[0]);
-          } else if (base >= half) {
-            dhi = dhi + clip(v4.x, p.lo[1], p.hi[1]);
-            dhi = dhi + clip(v4.y, p.lo[1], p.hi[1]);
-            dhi = dhi + clip(v4.z, p.lo[1], p.hi[1]);
-            dhi = dhi + clip(v4.w, p.lo[1], p.hi[1]);
-          } else {
-            const float v[4] = {v4.x, v4.y, v4.z, v4.w};
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-              if (base + k < half) dlo = dlo + clip(v[k], p.lo[0], p.hi[0]);
-              else dhi = dhi + clip(v[k], p.lo[1], p.hi[1]);
-            }
-          }
+        float4 v4;
+        if (GEN0) {
+          v4 = make_genes<true>(p, Pair{}, g, jp[i], base);
+        } else {
+          const float4 t1 = *reinterpret_cast<const float4*>(row(row1[i]) + base);
+          const float4 t2 = *reinterpret_cast<const float4*>(row(row2[i]) + base);
+          const PhiloxIndividual w = philox_individual((uint32_t)jp[i], g, p.key);
+          v4 = vary4(t1, t2, philox_finish(item, w, p.key), p.iso_sigma, lambda[i], tb);
         }
-      } else {
-        // ragged last block
+        if (KEEP) *reinterpret_cast<float4*>(p.off_geno + (size_t)jp[i] * (size_t)p.stride + base) = v4;
+        if (TASK != kTaskProj) {
+          g0[i] = v4.x;
+          g1[i] = v4.y;
+        }
         const float v[4] = {v4.x, v4.y, v4.z, v4.w};
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-          const int gi = base + k;
-          if (gi < n) {
-            acc = acc + task_term<TASK>(v[k]);
-            if (TASK == kTaskProj) {
-              if (gi < half) dlo = dlo + clip(v[k], p.lo[0], p.hi[0]);
-              else dhi = dhi + clip(v[k], p.lo[1], p.hi[1]);
-            }
+          if (base + k >= n) continue;
+          acc[i] = acc[i] + task_term<TASK>(v[k]);
+          if (TASK == kTaskProj) {
+            if (base + k < half) g0[i] = g0[i] + clip(v[k], p.lo[0], p.hi[0]);
+            else g1[i] = g1[i] + clip(v[k], p.lo[1], p.hi[1]);
           }
         }
       }
     }
-    // folded sums (wave-uniform); lane i keeps offspring i's, and divides the
-    // half sums once after the loop
-    float f, d0, d1;
-    if (TASK == kTaskProj) {
-      wave_fold_sum3(acc, dlo, dhi, f, d0, d1);
+    f = fold_halves<OPW>(acc);
+    if constexpr (TASK == kTaskProj) {
+      d0 = fold_halves<OPW>(g0) / (float)half;
+      d1 = fold_halves<OPW>(g1) / (float)(n - half);
     } else {
-      f = wave_fold_sum(acc);
-      d0 = clip(__uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(g0), 0)), p.lo[0], p.hi[0]);
-      d1 = clip(__uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(g1), 0)), p.lo[1], p.hi[1]);
+      // from the first lane of each half to the first row of its part
+      if constexpr (OPW == 4) {
+        d0 = rows_from_halves(g0[0], g0[1]);
+        d1 = rows_from_halves(g1[0], g1[1]);
+      } else {
+        d0 = g0[0];
+        d1 = g1[0];
+      }
+      d0 = clip(row_first(d0), p.lo[0], p.hi[0]);
+      d1 = clip(row_first(d1), p.lo[1], p.hi[1]);
     }
-    if (lane == i) {
-      my_f = -f;
-      my_d0 = d0;
-      my_d1 = d1;
+  } else {
+    // what the wave needs of each offspring, in scalar registers
+    const float* row1[OPW];
+    const float* row2[OPW];
+    float lambda[OPW];
+    int jp[OPW];
+#pragma unroll
+    for (int i = 0; i < OPW; ++i) {
+      row1[i] = row(row_of(from_lane(par1, i * LPO)));
+      row2[i] = row(row_of(from_lane(par2, i * LPO)));
+      lambda[i] = from_lane(sel_lambda, i * LPO);
+      jp[i] = from_lane(my_j, i * LPO);
+    }
+    // Term sums; with a projection also the running clipped sum of the half that
+    // the lane's genes are in, and the lower half's once the lane is past it.
+    float acc[OPW], run[OPW], low[OPW], g0 = 0.0f, g1 = 0.0f;
+#pragma unroll
+    for (int i = 0; i < OPW; ++i) acc[i] = run[i] = low[i] = 0.0f;
+    const auto pass_half = [&](bool now) {
+#pragma unroll
+      for (int i = 0; i < OPW; ++i) {
+        low[i] = now ? run[i] : low[i];
+        run[i] = now ? 0.0f : run[i];
+      }
+    };
+    const int nchunks = (n + 255) >> 8, half_chunk = half >> 8;
+    // the lane's four genes of a chunk, for every offspring; split: single genes
+    // are told apart, as a block straddles the genotype's end or middle
+    const auto chunk = [&](auto split, bool first, int base, bool lower, auto from_i, auto to_i) {
+      const float blo = TASK != kTaskProj || lower ? p.lo[0] : p.lo[1];
+      const float bhi = TASK != kTaskProj || lower ? p.hi[0] : p.hi[1];
+      PhiloxItem item{};
+      if (!GEN0) item = philox_item((uint32_t)(base >> 2), g, kTagIso, p.key);
+      const uint32_t off = 4u * (uint32_t)base;
+#pragma unroll
+      for (int i = decltype(from_i)::value; i < decltype(to_i)::value; ++i) {
+        float4 v4;
+        int j = jp[i];
+        if (GEN0) {
+          v4 = make_genes<true>(p, Pair{}, g, j, base);
+        } else {
+          // wave-uniform row pointer + 32-bit unsigned byte offset (rows are far
+          // below 4 GiB): a scalar base and a vector offset
+          const float4 t1 = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(row1[i]) + off);
+          const float4 t2 = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(row2[i]) + off);
+          hold_scalar(j);   // (kept for the whole loop, its products would cost a wave per SIMD)
+          const PhiloxIndividual w = philox_individual((uint32_t)j, g, p.key);
+          v4 = vary4(t1, t2, philox_finish(item, w, p.key), p.iso_sigma, lambda[i], tb);
+        }
+        if (KEEP) *reinterpret_cast<float4*>(p.off_geno + (size_t)j * (size_t)p.stride + base) = v4;
+        if (TASK != kTaskProj && first) {   // genes 0 and 1, from lane 0 to lane 8 i
+          g0 = lane == 8 * i ? from_lane(v4.x, 0) : g0;
+          g1 = lane == 8 * i ? from_lane(v4.y, 0) : g1;
+        }
+        const float v[4] = {v4.x, v4.y, v4.z, v4.w};
+        if (!split) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) acc[i] = acc[i] + task_term<TASK>(v[k]);
+          if (TASK == kTaskProj) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) run[i] = run[i] + clip(v[k], blo, bhi);
+          }
+        } else {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            if (base + k >= n) continue;
+            acc[i] = acc[i] + task_term<TASK>(v[k]);
+            if (TASK == kTaskProj) {
+              if (lower && base + k == half) {
+                low[i] = run[i];
+                run[i] = 0.0f;
+              }
+              const bool in_low = base + k < half;
+              run[i] = run[i] + clip(v[k], in_low ? p.lo[0] : p.lo[1], in_low ? p.hi[0] : p.hi[1]);
+            }
+          }
+        }
+        hold(acc[i]);   // done here: no offspring's genes wait for the next one's
+      }
+    };
+    const auto chunks = [&](auto from_i, auto to_i) {
+#pragma unroll 1
+        for (int c = 0; c < nchunks; ++c) {
+        const int base = 256 * c + 4 * lane;
+        const bool lower = base < half;
+        if (TASK == kTaskProj && c == half_chunk) pass_half(!lower);
+        const bool split = (256 * c + 256 > n && (n & 3) != 0) ||
+                           (TASK == kTaskProj && c == half_chunk && (half & 3) != 0);
+        if (base < n) {
+  // Large batches of projections have a copy of the code without the
+          // split (n = 1000, N_B = 65536: 57.0 us against 57.8 us with one copy and
+          // a branch); a small batch's launch waits for each further line of code
+          // from memory (n = 777, N_B = 3001: 16.2 us a generation with two, 15.5 us
+          // with one), and the other tasks lose registers to it (Rastrigin, n = 300,
+          // N_B = 65536: 38.3 and 36.6 us).
+          if constexpr (OPW == 4 && TASK == kTaskProj) {
+            if (!split) chunk(std::false_type{}, c == 0, base, lower, from_i, to_i);
+            else chunk(std::true_type{}, c == 0, base, lower, from_i, to_i);
+          } else {
+            chunk(split, c == 0, base, lower, from_i, to_i);
+          }
+        }
+        if (TASK == kTaskProj && c == half_chunk) pass_half(base + 4 <= half);
+      }
+    };
+    if constexpr (TASK == kTaskSphere && OPW == 4) {
+      // With so little to work out per gene, reading the rows is what takes the
+      // time, and a row read whole is quicker than four in turns (n = 400 on
+      // 10^4 filled cells, 60000 offspring: 34.7 us against 35.6 us).
+      chunks(index<0>{}, index<1>{});
+      chunks(index<1>{}, index<2>{});
+      chunks(index<2>{}, index<3>{});
+      chunks(index<3>{}, index<4>{});
+    } else {
+      chunks(index<0>{}, index<OPW>{});
+    }
+    f = fold_offspring<OPW>(acc);
+    if (TASK == kTaskProj) {
+      d0 = fold_offspring<OPW>(low) / (float)half;
+      d1 = fold_offspring<OPW>(run) / (float)(n - half);
+    } else {
+#pragma unroll
+      for (int i = 0; i < OPW; ++i) {
+        d0 = part == i ? from_lane(g0, 8 * i) : d0;
+        d1 = part == i ? from_lane(g1, 8 * i) : d1;
+      }
+      d0 = clip(d0, p.lo[0], p.hi[0]);
+      d1 = clip(d1, p.lo[1], p.hi[1]);
     }
   }
-  if (TASK == kTaskProj) {
-    my_d0 = my_d0 / (float)half;
-    my_d1 = my_d1 / (float)(n - half);
-  }
-  const int listed = p.tess == kTessCvt && p.cand_res > 0 ? cvt_cell_rows(p, my_d0, my_d1, lane) : -2;
-  if (mine) {
-    const int j = j0 + lane;
-    const float d[2] = {my_d0, my_d1};
+  f = -f;
+  const int listed = p.tess == kTessCvt && p.cand_res > 0 ? cvt_cell_rows(p, d0, d1, lane) : -2;
+  if (speaks) {
+    const float d[2] = {d0, d1};
     int cell = -1;
-    if (my_f == my_f) {
+    if (f == f) {
       if (p.tess == kTessGrid) cell = grid_cell(p, d);
       else cell = listed != -2 ? listed : cvt_cell<2>(p, d);
     }
-    const uint64_t key = insert_key(p, my_f, cell, j);
-    record_offspring(p, j, sel, my_f, d);
-    p.off_cell[j] = cell;
-    p.off_key[j] = key;
+    const uint64_t key = insert_key(p, f, cell, my_j);
+    Pair q{};
+    q.c1 = GEN0 ? -1 : par1 & ((1 << kBankBit) - 1);
+    q.c2 = GEN0 ? -1 : par2 & ((1 << kBankBit) - 1);
+    q.banks = GEN0 ? 0u : (uint32_t)(par1 >> kBankBit) | ((uint32_t)(par2 >> kBankBit) << 1);
+    record_offspring(p, my_j, q, f, d);
+    p.off_cell[my_j] = cell;
+    p.off_key[my_j] = key;
     insert_one(p, cell, key);
   }
 }

@@ -142,11 +142,6 @@ __device__ __forceinline__ float quad_dot(const float (&w)[R][M], const float4 (
   return quad_fold<R>(acc);
 }
 
-// Keeps a value in a register of its own (an empty asm that claims to change
-// it): the optimiser no longer derives other registers from how it was made.
-template <class T>
-__device__ __forceinline__ void hold(T& v) { __asm__ volatile("" : "+v"(v)); }
-
 // A pair that is the same in every lane of the wave, moved to scalar registers.
 __device__ __forceinline__ Pair uniform_pair(const Params& p, const Pair& v) {
   Pair q = v;

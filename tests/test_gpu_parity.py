@@ -118,6 +118,37 @@ def test_lloyd_centroids_bit_exact(C, D, S, L):
     assert np.any(got != q.centroids()), "Lloyd iterations moved no centroid"
 
 
+@pytest.mark.parametrize("task,n,nb", [
+    # one offspring per wave: block and chunk ends of the genotype and of its half
+    (W.RASTRIGIN_PROJ, 2, 1), (W.RASTRIGIN_PROJ, 7, 3), (W.RASTRIGIN_PROJ, 255, 5), (W.RASTRIGIN_PROJ, 258, 5),
+    (W.RASTRIGIN_PROJ, 514, 9), (W.RASTRIGIN_PROJ, 1029, 3), (W.RASTRIGIN, 128, 2), (W.SPHERE, 129, 3),
+    # two per wave, the last wave with one
+    (W.RASTRIGIN, 30, 2049), (W.RASTRIGIN_PROJ, 131, 2051), (W.SPHERE, 260, 2049),
+    # four per wave, the last wave with one, two and three
+    (W.SPHERE, 5, 8193), (W.RASTRIGIN, 127, 8195), (W.RASTRIGIN, 133, 8194), (W.RASTRIGIN_PROJ, 250, 8193),
+    (W.RASTRIGIN_PROJ, 777, 8195), (W.RASTRIGIN_PROJ, 3, 8194), (W.RASTRIGIN_PROJ, 127, 8193),
+    (W.RASTRIGIN_PROJ, 128, 8195), (W.SPHERE, 399, 8194), (W.RASTRIGIN, 513, 8195),
+])
+def test_genes_ragged(task, n, nb):
+    """Ragged genotype lengths and batches, with kept genotypes, against the
+    oracle: the first batch and one generation."""
+    w = W.workload("rastrigin_proj_cvt_b65536", task=task, n=n, batch=nb, C=300, seed=11,
+                   init_lo=-5.12, init_hi=5.12)
+    say(f"ragged genes task={task} n={n} N_B={nb}")
+    a = qd().Archive(w, keep_offspring=True)
+    o = O.Oracle(w)
+    o.init()
+    for g in (0, 1):
+        if g:
+            a.generation(g)
+            o.generation(g)
+        gb, ob = a.last_batch(), o.last_batch()
+        np.testing.assert_array_equal(gb["geno"], o.last_offspring(), err_msg=f"generation {g}")
+        for k in ("fit", "desc", "cell", "won"):
+            np.testing.assert_array_equal(gb[k], ob[k], err_msg=f"{k} of generation {g}")
+    assert_archive_equal(a.snapshot(), o.archive(), o.n, "after one generation")
+
+
 @pytest.mark.parametrize("C,S,L", [
     (1, 10, 1), (2, 1, 2), (3, 100, 3), (5, 4000, 2),      # grids of one and two buckets a side
     (5, 1 << 20, 1), (5, (1 << 20) + 1, 2),                # count packed into a sum's word, and apart
