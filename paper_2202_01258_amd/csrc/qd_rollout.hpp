@@ -223,8 +223,8 @@ __device__ __forceinline__ void flush_ring(float (*ra)[A], float (*rs)[kRing + 1
 // wait for the first layer).  At three waves per SIMD (64 wide) the SIMD issues
 // one VALU instruction per ~3 cycles, 280 a step.  Measured, one generation
 // with the earlier layout (inputs broadcast inside DPP fmas, a row per lane)
-// and this one: 64 wide, T = 250: 256 individuals 228 -> 200 us, 8192: 860 ->
-// 762 us (36.6 -> 41.3 TFLOP/s); 128 wide, T = 400: 256: 448 -> 410 us, 1501:
+// and this one: 64 wide, T = 250: 256 individuals 233 -> 202 us, 8192: 913 ->
+// 762 us (34 -> 41 TFLOP/s); 128 wide, T = 400: 256: 448 -> 391 us, 1501:
 // 1052 -> 928 us, 16384: 8165 -> 7420 us.
 template <int H, int W>
 struct RolloutShape {
@@ -564,7 +564,7 @@ __global__ __launch_bounds__(256) void k_regen_mlp(const Params p, uint32_t g) {
 // individuals and 250 steps, 239 and 340 us against 239 us for 1024).  128
 // wide: two, whose weights leave room for two waves per SIMD, or eight of one
 // row per quad while there is at most one individual per CU (64 to 256
-// individuals, 400 steps: 410 us against 436 us; 512: 590 against 470 us).
+// individuals, 400 steps: 391 us against 436 us; 512: 590 against 470 us).
 constexpr int kEightWaveBatch = 256;
 
 template <int H, class Go>
