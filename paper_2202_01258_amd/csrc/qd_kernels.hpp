@@ -1208,15 +1208,18 @@ __global__ void k_bucket_count(const Params p) {
 // chain over the dimensions, first minimum in index order).  Each point adds
 // its coordinates' 24-bit numerators and a count to its centroid's
 // accumulators -- integer sums, so the order of the atomics does not matter.
-// Up to 2^kLloydSumBits / 2^24 points the count goes above coordinate 0's sum in
-// one word: the atomics are what an iteration in two dimensions takes its time
-// for (100000 points: 25 us with three per point, 20 us with two).
+// With fewer than 2^20 points the count goes above coordinate 0's sum in one
+// word: all of them in one cell sum to less than 2^(20 + 24) = 2^kLloydSumBits,
+// and their count fits the 64 - kLloydSumBits = 20 bits above (2^20 points in
+// one cell would not).  The atomics are what an iteration in two dimensions takes
+// its time for (100000 points: 25 us with three per point, 20 us with two).
 constexpr int kLloydBlock = 256;
 constexpr int kLloydTile = 1024;
 constexpr int kLloydSumBits = 44;
 
 __device__ __forceinline__ bool lloyd_packed(const Params& p) {
-  return p.cvt_samples <= (1 << (kLloydSumBits - 24));
+  static_assert(kLloydSumBits - 24 == 64 - kLloydSumBits, "the sum and the count have the same limit");
+  return p.cvt_samples < (1 << (64 - kLloydSumBits));
 }
 
 template <int D>

@@ -167,6 +167,20 @@ def test_lloyd_lists_bit_exact(C, S, L):
     np.testing.assert_array_equal(a.last_batch()["cell"], o.last_batch()["cell"])
 
 
+@pytest.mark.parametrize("D", [2, 4])
+@pytest.mark.parametrize("S", [(1 << 20) - 1, 1 << 20, (1 << 20) + 1])
+def test_lloyd_count_of_one_cell_at_the_packed_limit(D, S):
+    """One cell gets all the points: its count and sums at and around the number
+    of points from which the count has a word of its own."""
+    base = "rastrigin_proj_cvt_b65536" if D == 2 else "mlp64_cvt_b8192"
+    w = W.workload(base, C=1, batch=16, cvt_samples=S, cvt_iters=1, seed=2)
+    say(f"lloyd one cell D={D} S={S}")
+    a = qd().Archive(w)
+    o = O.Oracle(w)
+    o.setup()
+    np.testing.assert_array_equal(a.views()["centroids"].cpu().numpy(), o.centroids())
+
+
 @pytest.mark.parametrize("C,L", [(1, 0), (2, 0), (3, 2), (37, 0), (500, 3), (3003, 0)])
 def test_cvt_candidate_lists_complete(C, L):
     """A fine bucket's count and list are those of the definition worked out
