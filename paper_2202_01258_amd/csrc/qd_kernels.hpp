@@ -978,20 +978,38 @@ __device__ void compact_filled(const Params& p) {
 }
 
 // ---------------------------------------------------------------------------
-// Winners: a workgroup takes kRegenCells consecutive cells, kRegenCellsPerWave
-// to each of its four waves.  For each of its cells whose key names an
-// offspring, a wave regenerates that offspring's genotype into the cell's
-// other bank from the recorded parents; then the wave's cells record
-// objective and descriptor, switch to the new bank, and turn the key into the
-// incumbent form (low word all ones: a later offspring must be strictly
-// better).  No other wave touches those cells.
+// Winners: a workgroup takes CELLS consecutive cells, of which some name an
+// offspring in their key.  kRegenCellsDense: two to each of its four waves.
+// kRegenCells: those that name one are dealt to the waves in turn, so that
+// winners in neighbouring cells run beside one another.  For each of its
+// winners a wave regenerates the offspring's genotype into the cell's other
+// bank from the recorded parents; then the wave's cells record objective and
+// descriptor, switch to the new bank, and turn the key into the incumbent form
+// (low word all ones: a later offspring must be strictly better).  No other
+// wave touches those cells.
 // ---------------------------------------------------------------------------
-// Two cells per wave: where many cells change hands a wave's winners come one
-// after another, a chain of round trips each (with eight per wave: N_B = 65536,
-// n = 100 on 10^4 cells 9.8 us against 7.2 us, n = 1000 14.4 against 9.0 us while
-// the archive fills, 4.0 us both when nothing is won).
-constexpr int kRegenCellsPerWave = 2;
+// 32 cells per workgroup, whose winners come four at a time: most launches find
+// few of them, and what a launch then costs is its workgroups (and the wait of
+// the compacting workgroup, the last one, behind them).  It also keeps the grid
+// of the largest archive, 2^28 cells, at 2^31 threads, where a launch takes fewer
+// than 2^32.  A small archive with a batch of at least half its cells has
+// winners in many of them, each a chain of round trips; there 8 cells put all of
+// a workgroup's in flight in two turns.  Both measured, one generation, n = 16,
+// archive filling from a wide first batch (8 cells | 32 cells, us):
+//   C = 1000   N_B = 1024 11.8 | 13.1, 16384 15.5 | 17.6, 65536 24.4 | 27.0
+//   C = 3000   N_B = 1024 12.8 | 13.0,  4096 13.4 | 14.8, 65536 24.9 | 27.2
+//   C = 10000  N_B = 1024 22.3 | 22.0, 16384 15.6 | 15.8, 65536 25.0 | 25.9
+//   C = 20000  N_B = 1024 31.8 | 31.1, 16384 23.6 | 22.7, 65536 32.3 | 31.6
+//   C = 90000  N_B = 1024  102 | 98.3, 16384  137 |  130, 65536  157 |  148
+constexpr int kRegenCellsPerWave = 8;
 constexpr int kRegenCells = 4 * kRegenCellsPerWave;
+constexpr int kRegenCellsDense = 8;
+constexpr int kRegenDenseMax = 16384;
+
+// Cells per workgroup of a launch.
+inline int regen_cells(int nb, int C) {
+  return C <= kRegenDenseMax && nb >= C / 2 ? kRegenCellsDense : kRegenCells;
+}
 
 __device__ __forceinline__ void finish_winner(const Params& p, int c, int j, uint64_t key) {
   p.arch_fit[c] = p.off_fit[j];
@@ -1023,27 +1041,32 @@ __device__ __forceinline__ bool stage_keys(const Params& p, int first, uint64_t*
 // Workgroups 0 .. ceil(C / cells) - 1 take cells; one more compacts.
 inline unsigned regen_blocks(int C, int cells) { return (unsigned)((C + cells - 1) / cells) + 1u; }
 
-template <bool GEN0>
+template <bool GEN0, int CELLS>
 __global__ __launch_bounds__(256) void k_regen(const Params p, uint32_t g) {
+  constexpr bool DEAL = CELLS != kRegenCellsDense;
+  constexpr int LANES = DEAL ? CELLS : CELLS / 4;   // of a wave, each with a cell
+  static_assert(LANES <= 64, "a lane per cell");
   if (blockIdx.x == gridDim.x - 1) {
     compact_filled(p);
     return;
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int first = blockIdx.x * kRegenCells;
-  __shared__ uint64_t s_key[kRegenCells];
+  const int first = blockIdx.x * CELLS;
+  __shared__ uint64_t s_key[CELLS];
   __shared__ float4 s_ntab[kNormalRows];
-  if (!stage_keys<kRegenCells>(p, first, s_key)) return;
-  const int wfirst = first + wave * kRegenCellsPerWave;
-  const uint64_t* w_key = s_key + wave * kRegenCellsPerWave;
-  // lane t < kRegenCellsPerWave reads what its cell's winner recorded (test
-  // functions have two descriptor components), in flight with the table's loads
-  const uint64_t my_key = lane < kRegenCellsPerWave ? w_key[lane] : 0ull;
-  const bool my_won = names_offspring(my_key);
+  if (!stage_keys<CELLS>(p, first, s_key)) return;
+  // lane t reads what its cell's winner recorded (test functions have two
+  // descriptor components), in flight with the table's loads; dealt winners:
+  // the workgroup's i-th goes to wave i mod 4
+  const uint64_t* w_key = s_key + (DEAL ? 0 : wave * LANES);
+  const int wfirst = first + (DEAL ? 0 : wave * LANES);
+  const uint64_t my_key = lane < LANES ? w_key[lane] : 0ull;
+  bool mine = names_offspring(my_key);
+  if (DEAL) mine = mine && (__popcll(__ballot(mine) & ((1ull << lane) - 1ull)) & 3) == wave;
   const int my_j = p.nb - 1 - (int)(uint32_t)my_key;
   int par1 = 0, par2 = 0, banks = 0, slot = 0;
   float fit = 0.0f, desc[2] = {0.0f, 0.0f};
-  if (my_won) {
+  if (mine) {
     if (!GEN0) {
       par1 = p.off_par[2 * my_j];
       par2 = p.off_par[2 * my_j + 1];
@@ -1059,22 +1082,24 @@ __global__ __launch_bounds__(256) void k_regen(const Params p, uint32_t g) {
     __syncthreads();
   }
   const Tables tb{s_ntab};
-  for (int t = 0; t < kRegenCellsPerWave; ++t) {
-    const uint64_t key = w_key[t];
-    if (!names_offspring(key)) continue;
-    const int c = wfirst + t;
-    const int j = p.nb - 1 - (int)(uint32_t)key;
+  // (two cells are gone through by number: by the set bits, 74.4 us against 74.0 us
+  // for five generations of 3001 offspring, n = 777, on 3003 cells)
+  uint64_t todo = DEAL ? __ballot(mine) : 0ull;
+  for (int i = 0; DEAL ? todo != 0ull : i < LANES; ++i, todo &= todo - 1ull) {
+    const int t = DEAL ? __ffsll((unsigned long long)todo) - 1 : i;
+    if (!DEAL && !names_offspring(w_key[t])) continue;
+    const int j = __builtin_amdgcn_readlane(my_j, t);
     Pair q{nullptr, nullptr, 0.0f, -1, -1, 0u};
     if (!GEN0)
       q = pair_from_record(p, g, j, __builtin_amdgcn_readlane(par1, t),
                            __builtin_amdgcn_readlane(par2, t),
                            (uint32_t)__builtin_amdgcn_readlane(banks, t), tb);
-    float* dst = geno_row(p, (uint32_t)__builtin_amdgcn_readlane(slot, t) ^ 1u, c);
+    float* dst = geno_row(p, (uint32_t)__builtin_amdgcn_readlane(slot, t) ^ 1u, wfirst + t);
     for (int base = 4 * lane; base < p.n; base += 256)
       *reinterpret_cast<float4*>(dst + base) = make_genes<GEN0>(p, q, g, j, base);
   }
   // then lane t finishes its cell: objective, descriptor, bank, incumbent key
-  if (my_won) {
+  if (mine) {
     const int c = wfirst + lane;
     p.arch_fit[c] = fit;
     p.arch_desc[2 * (size_t)c] = desc[0];

@@ -353,8 +353,10 @@ void launch_regen(qd_archive* h, hipStream_t s, uint32_t g) {
   if (p.task == qd::kTaskMlp) {
     qd::launch_mlp_regen(p, GEN0, g, go);
   } else {
-    const dim3 grid(qd::regen_blocks(p.C, qd::kRegenCells)), block(256);
-    go(qd::k_regen<GEN0>, grid, block, p, g);
+    const int cells = qd::regen_cells(p.nb, p.C);
+    const dim3 grid(qd::regen_blocks(p.C, cells)), block(256);
+    if (cells == qd::kRegenCellsDense) go(qd::k_regen<GEN0, qd::kRegenCellsDense>, grid, block, p, g);
+    else go(qd::k_regen<GEN0, qd::kRegenCells>, grid, block, p, g);
   }
 }
 

@@ -149,6 +149,31 @@ def test_genes_ragged(task, n, nb):
     assert_archive_equal(a.snapshot(), o.archive(), o.n, "after one generation")
 
 
+@pytest.mark.parametrize("grid,nb", [
+    ((1, 1), 3), ((7, 1), 40), ((1, 9), 200),               # 8 cells per workgroup: its ends,
+    ((128, 128), 8192),                                     # the last cell count and batch that take it
+    ((128, 128), 8191), ((145, 113), 20000),                # 32: the first batch and cell count past those
+    ((31, 1), 14), ((32, 1), 15), ((33, 1), 15), ((65, 1), 31),
+])
+def test_winner_kernel_cells_per_workgroup(grid, nb):
+    """Both choices of cells per workgroup at the ends of their ranges: first
+    batch and three generations against the oracle."""
+    w = W.workload("rastrigin_grid_b128", n=7, batch=nb, grid=grid, C=grid[0] * grid[1], seed=9,
+                   init_lo=-5.12, init_hi=5.12)
+    say(f"winner kernel grid={grid} N_B={nb}")
+    a = qd().Archive(w)
+    o = O.Oracle(w)
+    o.init()
+    for g in range(4):
+        if g:
+            a.generation(g)
+            o.generation(g)
+        gb, ob = a.last_batch(), o.last_batch()
+        for k in ("fit", "desc", "cell", "won"):
+            np.testing.assert_array_equal(gb[k], ob[k], err_msg=f"{k} of generation {g}")
+    assert_archive_equal(a.snapshot(), o.archive(), o.n, "after three generations")
+
+
 @pytest.mark.parametrize("C,S,L", [
     (1, 10, 1), (2, 1, 2), (3, 100, 3), (5, 4000, 2),      # grids of one and two buckets a side
     (5, 1 << 20, 1), (5, (1 << 20) + 1, 2),                # count packed into a sum's word, and apart

@@ -141,6 +141,39 @@ def test_regen_cells(C, kind):
         assert K["kRegenCells"] == 4 * K["kRegenCellsPerWave"] and K["kRegenCells"] <= 256
 
 
+def regen_cells(nb, C):
+    """The library's choice (regen_cells in qd_kernels.hpp)."""
+    dense = C <= K.get("kRegenDenseMax", 0) and nb >= C // 2
+    return K["kRegenCellsDense"] if dense else K["kRegenCells"]
+
+
+def test_winner_grid_in_range():
+    """A launch takes fewer than 2^32 threads: k_regen's grid stays below for
+    every accepted number of cells (up to 2^28) and any batch."""
+    edge = K.get("kRegenDenseMax", 1)
+    for C in [1, edge, edge + 1] + [1 << k for k in range(29)] + [(1 << k) - 1 for k in range(1, 29)]:
+        for nb in (1, max(1, C // 2 - 1), max(1, C // 2), C, 65536, (1 << 31) - 1):
+            cells = regen_cells(nb, C)
+            assert (ceil_div(C, cells) + 1) * 256 < 1 << 32, (C, nb, cells)
+
+
+def test_winners_dealt_to_waves():
+    """k_regen with kRegenCells: lane t of every wave holds cell first + t;
+    winner i of the workgroup goes to wave i mod 4.  Every winner goes to
+    exactly one wave."""
+    n = K["kRegenCells"]
+    assert n <= 64 and K["kRegenCellsDense"] % 4 == 0
+    rng = np.random.default_rng(0)
+    for won in [0, 1, (1 << n) - 1, 1 << (n - 1)] + [int(rng.integers(1 << n)) for _ in range(50)]:
+        taken = np.zeros(n, np.int64)
+        for wave in range(4):
+            for t in range(n):
+                rank = bin(won & ((1 << t) - 1)).count("1")
+                if (won >> t) & 1 and (rank & 3) == wave:
+                    taken[t] += 1
+        np.testing.assert_array_equal(taken, [(won >> t) & 1 for t in range(n)])
+
+
 def test_insert_hash_always_has_a_free_slot():
     """k_insert: a workgroup of kInsertBlock offspring sees at most that many
     distinct cells, so its open-addressing table of kInsertSlots entries
