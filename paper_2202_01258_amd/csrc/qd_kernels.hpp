@@ -476,10 +476,11 @@ template <int I>
 using index = std::integral_constant<int, I>;
 
 template <int TASK, bool GEN0, bool KEEP, int OPW>
-__global__ __launch_bounds__(256, OPW < 4 ? 1 : (TASK == kTaskProj ? 7 : 8))
+__global__ __launch_bounds__(256, OPW < 4 ? 1 : (TASK == kTaskProj ? (GEN0 && KEEP ? 6 : 7) : 8))
 void k_vary_eval(const Params p, uint32_t g) {
   // (seven waves per SIMD for projections: 70 registers; held at eight, spills
-  // cost more than the wave brings, 59.5 us against 57.0 us at n = 1000)
+  // cost more than the wave brings, 59.5 us against 57.0 us at n = 1000; a kept
+  // first batch needs 74 and has six, as no kernel may need scratch memory)
   static_assert(OPW == 1 || OPW == 2 || OPW == kOffspringPerWave, "one, two or four offspring");
   constexpr int LPO = 64 / OPW;            // lanes that speak for an offspring
   __shared__ float4 s_ntab[kNormalRows];

@@ -28,6 +28,16 @@ def test_exports_every_declared_symbol(lib):
         assert hasattr(lib, name)
 
 
+def test_no_kernel_needs_scratch_memory(lib):
+    """Every kernel's code object entry asks for no scratch memory per lane
+    (registers spilled to it; its first launch would have to allocate)."""
+    key = b".private_segment_fixed_size"          # a msgpack map entry: key, then an integer
+    data = open(Q.LIB_PATH, "rb").read()
+    sizes = [data[m.end()] for m in re.finditer(re.escape(key), data)]
+    assert len(sizes) > 60                        # every kernel instance
+    assert all(size == 0 for size in sizes), sizes
+
+
 def test_struct_layouts_match_the_header(lib, tmp_path):
     """The ctypes mirrors have the C compiler's sizes and offsets."""
     import shutil
