@@ -266,10 +266,10 @@ qd_status qd_set_kernel_timing(qd_archive* h, uint32_t kernel_mask);
  * them.  ms and counts must hold QD_NUM_KERNELS entries. */
 qd_status qd_kernel_times(qd_archive* h, double* ms, int32_t* counts);
 
-/* Self-check of the short division sequences the kernels use in place of
- * IEEE division, over every input each can receive: mismatches[0] counts the
- * fp32 inputs of tanh (all 2^32) whose result differs from the IEEE-arithmetic
- * definition, mismatches[1] those of sigmoid in [-1, 1] (zeros mean
+/* Self-check of the rewritten arithmetic in the kernels, over every input each
+ * function can receive: mismatches[0] counts the fp32 inputs of tanh (all 2^32)
+ * whose result differs from the definition in IEEE arithmetic, mismatches[1]
+ * those of sigmoid in [-1, 1], whose division is a short sequence (zeros mean
  * bit-identical results).  d_scratch: 16 bytes of device memory owned by the
  * caller, 8-byte aligned.  Synchronises `stream`. */
 qd_status qd_check_fast_arith(void* d_scratch, void* stream, uint64_t* mismatches);

@@ -208,9 +208,9 @@ __device__ __forceinline__ float div_rcp(float a, float b) {
 }
 
 // tanh: odd Taylor polynomial through x^11 for |x| < 0.3,
-// else 1 - 2 / (e^{2|x|} + 1) with e^y by exp32's formula; the sign is copied
-// back.  FAST takes the quotient from div_rcp (same bits for every fp32 input).
-template <bool FAST = true>
+// else 1 - 2 / (e^{2|x|} + 1) with e^y by exp32's formula and an IEEE division;
+// the sign is copied back.  The definition, which qd_check_fast_arith compares
+// tanh32 with over all 2^32 inputs.
 __device__ __forceinline__ float tanh32_plain(float x) {
   const float a = __builtin_fabsf(x);
   float r;
@@ -223,15 +223,14 @@ __device__ __forceinline__ float tanh32_plain(float x) {
     r = fma32(a * a2, p, a);
   } else {
     const float d = exp32(a + a) + 1.0f;
-    r = 1.0f - (FAST ? div_rcp(2.0f, d) : 2.0f / d);
+    r = 1.0f - 2.0f / d;
   }
   return __builtin_copysignf(r, x);
 }
 
-// tanh32_plain<true> bit for bit (qd_check_fast_arith compares all 2^32
-// inputs), without its branch and with fewer instructions.  Nearly every wave
-// holds both kinds of lanes, so both sides are evaluated and one is selected:
-// two chains side by side instead of one after the other.
+// tanh32_plain bit for bit, without its branch and with fewer instructions.
+// Nearly every wave holds both kinds of lanes, so both sides are evaluated and
+// one is selected: two chains side by side instead of one after the other.
 //   * small side on x itself, every step being odd or even in x (the sign of
 //     a zero is put back with the others');
 //   * e^{2a}: with h = min(a, 44), the doubling goes into the constants (a
@@ -270,8 +269,8 @@ __device__ __forceinline__ float tanh32(float x) {
   return __builtin_copysignf(a >= 0.3f ? high : low, x);
 }
 
-// 1 / (1 + e^{-x}); FAST as for tanh32 (same bits for |x| <= 1, the range of
-// the tanh states it is applied to).
+// 1 / (1 + e^{-x}).  FAST takes the quotient from div_rcp (same bits for
+// |x| <= 1, the range of the tanh states it is applied to).
 template <bool FAST = true>
 __device__ __forceinline__ float sigmoid32(float x) {
   const float d = 1.0f + exp32(-x);
@@ -298,12 +297,8 @@ __device__ __forceinline__ void wave_sync() {
 // instructions, h = 8 .. 1 rotate within rows of 16 lanes (DPP).  Every step
 // leaves each lane holding its pair's sum (addition commutes, so both members
 // of a pair hold the same bits), and the total ends in every lane.
-// DPP within rows of 16 lanes: row_shl<N> gives lane l the value of lane
-// l + N (0 past the row's end), row_ror<N> that of lane (l - N) mod 16.
-template <int N>
-__device__ __forceinline__ float row_shl(float v) {
-  return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0x100 + N, 0xf, 0xf, false));
-}
+// DPP within rows of 16 lanes: row_ror<N> gives lane l the value of lane
+// (l - N) mod 16.
 template <int N>
 __device__ __forceinline__ float row_ror(float v) {
   return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0x120 + N, 0xf, 0xf, true));

@@ -4,7 +4,8 @@
 // first iteration runs the same kernels with the random-init genotype):
 //   k_vary_eval   a wave takes 4 offspring (1 in batches of at most 2048, 2 in
 //                 batches of at most 8192; two at a time, one per half-wave,
-//                 for genotypes of at most 128 genes): draws their parents
+//                 for genotypes of at most 128 genes, of projections only where
+//                 it takes 4): draws their parents
 //                 uniformly from the filled cells (Appendix A.2), runs Iso+LineDD
 //                 (Algorithm 2) gene by gene on coalesced float4 rows of both parents with
 //                 the objective / descriptor reduction (Appendix B.2) in the
@@ -17,7 +18,7 @@
 //                 CVT of at most 2048 cells, searched from LDS) or k_insert:
 //                 the same outputs; keys folded per wave (and per workgroup)
 //                 before the atomics.
-//   k_regen       a workgroup per few cells: a cell whose key now names an
+//   k_regen       a workgroup per 32 or 8 cells: a cell whose key now names an
 //                 offspring regenerates that offspring's genotype into the
 //                 cell's other genotype bank (the parents' banks were recorded
 //                 per offspring, so they stay readable), records objective and
@@ -687,14 +688,14 @@ void k_vary_eval(const Params p, uint32_t g) {
     };
     const auto chunks = [&](auto from_i, auto to_i) {
 #pragma unroll 1
-        for (int c = 0; c < nchunks; ++c) {
+      for (int c = 0; c < nchunks; ++c) {
         const int base = 256 * c + 4 * lane;
         const bool lower = base < half;
         if (TASK == kTaskProj && c == half_chunk) pass_half(!lower);
         const bool split = (256 * c + 256 > n && (n & 3) != 0) ||
                            (TASK == kTaskProj && c == half_chunk && (half & 3) != 0);
         if (base < n) {
-  // Large batches of projections have a copy of the code without the
+          // Large batches of projections have a copy of the code without the
           // split (n = 1000, N_B = 65536: 57.0 us against 57.8 us with one copy and
           // a branch); a small batch's launch waits for each further line of code
           // from memory (n = 777, N_B = 3001: 16.2 us a generation with two, 15.5 us
@@ -1268,10 +1269,10 @@ __device__ __forceinline__ void lloyd_add(const Params& p, int c, const uint32_t
 
 // Two dimensions: the exact ring search of cvt_cell, over the lists.  A ring's
 // lists are walked side by side, one round trip per node of the longest (about
-// every wave has a lane that needs ring 2).  A list holds about one centroid, so a point meets some nine of them
-// where all C were measured before: 100000 points on 10^4 centroids take
-// 20 us an iteration against 275 us, the bound now being the chain of
-// dependent loads and the atomics.
+// every wave has a lane that needs ring 2).  A list holds about one centroid, so
+// a point meets some nine of them where all C were measured before: 100000
+// points on 10^4 centroids take 20 us an iteration against 275 us, the bound now
+// being the chain of dependent loads and the atomics.
 __global__ __launch_bounds__(kLloydBlock) void k_lloyd_assign2(const Params p, int region) {
   const int i = blockIdx.x * kLloydBlock + threadIdx.x;
   const int* heads = lloyd_heads(p, region);
@@ -1592,10 +1593,10 @@ __global__ __launch_bounds__(256) void k_sample_normals(const float4* ntab, cons
     z[i] = normal(x[i], tb);
 }
 
-// Self-checks of the short division sequences against the IEEE operations,
-// over every input each one can receive: tanh for all 2^32 fp32 bit patterns,
-// sigmoid for all fp32 values in [-1, 1].  Counts results that differ (both
-// NaN = equal).
+// Self-checks over every input each function can receive: the kernels' tanh
+// against its definition for all 2^32 fp32 bit patterns, sigmoid's short division
+// against the IEEE one for all fp32 values in [-1, 1].  Counts results that
+// differ (both NaN = equal).
 __global__ void k_zero_u64(unsigned long long* x) {
   if (threadIdx.x < 2) x[threadIdx.x] = 0ull;
 }
@@ -1610,7 +1611,7 @@ __global__ __launch_bounds__(256) void k_check_fast(unsigned long long* count) {
   unsigned long long bad_t = 0, bad_s = 0;
   for (uint64_t k = tid; k < (1ull << 32); k += nthr) {
     const float x = __uint_as_float((uint32_t)k);
-    bad_t += same_bits(tanh32(x), tanh32_plain<false>(x)) ? 0 : 1;
+    bad_t += same_bits(tanh32(x), tanh32_plain(x)) ? 0 : 1;
     if (__builtin_fabsf(x) <= 1.0f) bad_s += same_bits(sigmoid32<true>(x), sigmoid32<false>(x)) ? 0 : 1;
   }
   if (bad_t) atomicAdd(count, bad_t);

@@ -21,8 +21,9 @@ namespace {
 thread_local hipError_t g_last_hip = hipSuccess;
 
 constexpr uint64_t kAlign = 256;
-// Candidate lists are built (one thread per fine bucket, each scanning every
-// centroid twice) only up to this many cells.
+// Candidate lists are built only up to this many cells: QD_CAND_SLOTS entries of
+// 16 bytes for each of four fine buckets per cell, 1 KiB per cell of workspace
+// (64 MiB here).  Larger archives go through the ring search alone.
 constexpr int kCandMaxCells = 65536;
 
 uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }

@@ -6,10 +6,10 @@
 // batch of independent GEMV chains, not one GEMM: no matrix core applies.
 //
 // One, two or eight waves run one individual with all its weights in VGPRs for
-// the whole episode.  The summation order of every output is fixed (hidden layers and A s: four
-// interleaved partial sums, then the bias; output layer: 8 slices folded
-// pairwise, then the bias; dynamics: A s + B a), which keeps the result
-// independent of the launch shape.
+// the whole episode.  The summation order of every output is fixed (hidden
+// layers and A s: four interleaved partial sums, then the bias; output layer: 8
+// slices folded pairwise, then the bias; dynamics: A s + B a), which keeps the
+// result independent of the launch shape.
 //
 // The genotype is produced in the kernel's prologue straight from the parents
 // (or the Glorot-uniform first batch) -- offspring weights never touch HBM.
@@ -223,8 +223,8 @@ __device__ __forceinline__ void flush_ring(float (*ra)[A], float (*rs)[kRing + 1
 // wait for the first layer).  At three waves per SIMD (64 wide) the SIMD issues
 // one VALU instruction per ~3 cycles, 280 a step.  Measured, one generation
 // with the earlier layout (inputs broadcast inside DPP fmas, a row per lane)
-// and this one: 64 wide, T = 250: 256 individuals 233 -> 202 us, 8192: 913 ->
-// 762 us (34 -> 41 TFLOP/s); 128 wide, T = 400: 256: 448 -> 391 us, 1501:
+// and this one: 64 wide, T = 250: 256 individuals 230 -> 202 us, 8192: 866 ->
+// 763 us (34 -> 39 TFLOP/s); 128 wide, T = 400: 256: 448 -> 391 us, 1501:
 // 1052 -> 928 us, 16384: 8165 -> 7420 us.
 template <int H, int W>
 struct RolloutShape {
@@ -570,7 +570,7 @@ constexpr int kEightWaveBatch = 256;
 template <int H, class Go>
 inline void launch_rollout_as(const Params& p, bool gen0, uint32_t g, bool keep, const Go& go) {
   using S = RolloutShape<H, rollout_waves(H)>;
-  const dim3 grid((unsigned)((p.nb + S::kInd - 1) / S::kInd)), block(S::kThreads);
+  const dim3 grid(((unsigned)p.nb + S::kInd - 1u) / S::kInd), block(S::kThreads);
   if (gen0) {
     if (keep) go(k_rollout<H, true, true>, grid, block, p, g);
     else go(k_rollout<H, true, false>, grid, block, p, g);

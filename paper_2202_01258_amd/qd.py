@@ -167,9 +167,9 @@ def normal_table():
 
 
 def check_fast_arith(device: str = "cuda:0") -> list:
-    """Mismatch counts of the short division sequences against IEEE
-    arithmetic: [tanh (all 2^32 inputs), sigmoid (|x| <= 1)], run on `device`
-    and its current stream."""
+    """Mismatch counts of the kernels' rewritten arithmetic against the
+    definitions in IEEE arithmetic: [tanh (all 2^32 inputs), sigmoid
+    (|x| <= 1)], run on `device` and its current stream."""
     import torch
     with torch.cuda.device(torch.device(device)):
         scratch = torch.zeros(2, dtype=torch.int64, device=device)
