@@ -176,7 +176,7 @@ def test_winner_kernel_cells_per_workgroup(grid, nb):
 
 @pytest.mark.parametrize("C,S,L", [
     (1, 10, 1), (2, 1, 2), (3, 100, 3), (5, 4000, 2),      # grids of one and two buckets a side
-    (5, 1 << 20, 1), (5, (1 << 20) + 1, 2),                # count packed into a sum's word, and apart
+    (5, (1 << 20) - 1, 1), (5, 1 << 20, 1), (5, (1 << 20) + 1, 2),   # count in a sum's word, and apart
     (4100, 255, 4), (4100, 30001, 1),                      # most cells without points; many rings
 ])
 def test_lloyd_lists_bit_exact(C, S, L):

@@ -93,8 +93,9 @@ def offspring_per_wave(nb):
 
 
 def test_offspring_per_wave_choice():
-    """Four per wave in large batches, fewer in small ones; the selection and
-    cell-search lanes (0 .. P-1, rows of 16 lanes for four offspring) hold P."""
+    """Four per wave in large batches, fewer in small ones; each offspring's
+    part of the wave (64 / P lanes) holds at least one row of 16 lanes, which
+    the cell search takes."""
     assert K["kOffspringPerWave"] == 4
     assert 0 < K["kOneOffspringBatch"] < K["kTwoOffspringBatch"]
     assert [offspring_per_wave(nb) for nb in (1, 2048, 2049, 8192, 8193, 65536)] == [1, 1, 2, 2, 4, 4]
@@ -107,8 +108,8 @@ def test_offspring_per_wave_choice():
 @pytest.mark.parametrize("nb", BATCHES)
 def test_vary_eval_offspring_lanes(nb):
     """k_vary_eval: grid ceil(nb / (4 P)) x 256; wave w of workgroup b takes
-    offspring j0 = (4 b + w) P .. j0 + nmine - 1, lane i < nmine speaking for
-    j0 + i."""
+    offspring j0 = (4 b + w) P .. j0 + nmine - 1, the first lane of the wave's
+    i-th 64 / P lanes, i < nmine, speaking for j0 + i."""
     P = offspring_per_wave(nb)
     blocks = ceil_div(nb, 4 * P)
     taken = np.zeros(nb, np.int64)
